@@ -162,6 +162,7 @@ struct sympix_kernel {
     double *u64 = nullptr;
     float *ut32 = nullptr;
     double *u64t = nullptr;
+    sympix::UnitMasks masks = {};
     void *block = nullptr;    // one stream-ordered allocation holding all of the above
 };
 
@@ -444,6 +445,7 @@ sympix_status sample_btnb(const sympix_grid *g, const sympix_kernel *d, const sy
     sympix::BtnbArgs a;
     a.u64t = b->u64t;
     a.ut32 = b->ut32;
+    a.masks = b->masks;
     if (pat) {
         const DevClasses *dc = nullptr;
         s = two_hop_tables(g, b->device, &pat, &dc);
@@ -461,12 +463,7 @@ sympix_status sample_btnb(const sympix_grid *g, const sympix_kernel *d, const sy
         a.mtiles = dg->gtiles;
     }
     a.nmtiles = (int64_t)ct.gtiles.size() / 4;
-    // A short FP64 launch runs faster on tiles of at most 32 rows: twice the tiles to
-    // balance over the CUs, and the FP64 kernel keeps its full speed on half tiles
-    if (!pat && prec == SYMPIX_FP64 && (int64_t)ct.mtiles.size() / 4 < sympix::kShortLaunchTiles) {
-        a.mtiles = dg->gtiles32;
-        a.nmtiles = (int64_t)ct.gtiles32.size() / 4;
-    }
+    a.max_terms = ct.max_class_terms;
     a.nblocks = nblocks;
     a.npix = geo.npix;
     a.ninv = ninv_dev;
@@ -525,7 +522,10 @@ sympix_status tabulate(const TabSource &src, const sympix_grid *g, const sympix_
     const size_t o_u64 = o_table + up((size_t)n_nodes * sizeof(double));
     const size_t o_u64t = o_u64 + up(nu * sizeof(double));
     const size_t o_ut32 = o_u64t + up(nu * sizeof(double));
-    const size_t total = o_ut32 + up(nu * sizeof(float));
+    const size_t o_units = o_ut32 + up(nu * sizeof(float));
+    const size_t o_cols = o_units + up((size_t)src.nunique * 64 * sizeof(uint16_t));
+    const size_t o_over = o_cols + up((size_t)src.nunique * 4 * sizeof(uint16_t));
+    const size_t total = o_over + up(sizeof(int32_t));
     hipError_t e = hipMallocAsync(&kr->block, total, st);
     if (e != hipSuccess) {
         kr->block = nullptr;
@@ -539,16 +539,17 @@ sympix_status tabulate(const TabSource &src, const sympix_grid *g, const sympix_
     kr->u64 = (double *)(base + o_u64);
     kr->u64t = (double *)(base + o_u64t);
     kr->ut32 = (float *)(base + o_ut32);
+    kr->masks = sympix::UnitMasks{(uint16_t *)(base + o_units), (uint16_t *)(base + o_cols), (int32_t *)(base + o_over)};
     e = upload_coefficients(device, coef, kr->coef, st);
     if (e != hipSuccess) {
         hipStreamSynchronize(st);
         free_kernel(kr);
         return hip_fail(e, "copying coefficients");
     }
-    e = sympix::launch_tabulate(kr->coef, lmax, kr->h, kr->table, n_nodes, st);
+    e = sympix::launch_tabulate(kr->coef, lmax, kr->h, kr->table, n_nodes, kr->masks.overflow, st);
     if (e == hipSuccess)
         e = sympix::launch_unique_eval(ktable(kr), src.uinfo, src.nunique, src.ring_theta, src.ring_sin, kr->u64,
-                                       kr->u64t, kr->ut32, st);
+                                       kr->u64t, kr->ut32, kr->masks, st);
     sympix_status s = after_launch(e, st, "tabulate / unique-block evaluation");
     if (s != SYMPIX_OK) {
         hipStreamSynchronize(st);
@@ -858,6 +859,7 @@ struct sympix_batch {
     int32_t schedule = SYMPIX_SCHED_XCD_QUEUES;
     int32_t tiling = SYMPIX_TILES_64;
     int32_t nworkgroups = 0;
+    int32_t max_terms = 1;              // most contraction terms of a class of any problem
     // per tile shape (sympix_tiling): problem descriptors, dispatch tables,
     // work items in natural order
     std::vector<sympix::ProblemDesc64> hdesc64[SYMPIX_NTILINGS]; // FP64
@@ -1026,6 +1028,7 @@ sympix_status capture_batch(sympix_batch *bt, int32_t s, int32_t t) {
     bl.counters = bt->d_counters;
     bl.persistent = s != SYMPIX_SCHED_PER_PROBLEM;
     bl.nworkgroups = bt->nworkgroups;
+    bl.max_terms = bt->max_terms;
 
     e = hipStreamBeginCapture(bt->cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
@@ -1104,8 +1107,9 @@ sympix_status sympix_batch_create(const sympix_problem *p, int32_t n, int32_t pr
         int rt = 0;
         if (hipRuntimeGetVersion(&rt) != hipSuccess) rt = 0;
         shape = std::string(prop.gcnArchName) + "|hip" + std::to_string(rt) + mode_name[prec];
+        for (int32_t i = 0; i < n; ++i) bt->max_terms = std::max(bt->max_terms, p[i].g->geo.cls.max_class_terms);
         int occ = 0;
-        e = sympix::batch_occupancy(prec, &occ);
+        e = sympix::batch_prepare(prec, bt->max_terms, &occ);
         if (e != hipSuccess) {
             free_batch(bt);
             return hip_fail(e, "occupancy query");
@@ -1124,7 +1128,8 @@ sympix_status sympix_batch_create(const sympix_problem *p, int32_t n, int32_t pr
             const int32_t *dtiles = t == SYMPIX_TILES_64 ? dg->mtiles : dg->mtiles32;
             const std::vector<int32_t> &tiles = t == SYMPIX_TILES_64 ? geo.cls.mtiles : geo.cls.mtiles32;
             sympix::ProblemDesc64 d64{dtiles, dg->classes, dg->class_terms, dg->class_blk, dg->class_itab,
-                                      p[i].b->u64t, p[i].ninv_dev, p[i].out_dev, nullptr, nullptr, nullptr};
+                                      p[i].b->u64t, p[i].ninv_dev, p[i].out_dev, nullptr, nullptr, nullptr,
+                                      p[i].b->masks.units, p[i].b->masks.cols, p[i].b->masks.overflow, bt->max_terms};
             bt->hdesc64[t].push_back(d64);
             sympix::ProblemDesc d{dtiles, dg->classes, dg->class_terms, dg->class_blk, dg->class_itab,
                                   p[i].b->ut32, nullptr, p[i].out_dev, nullptr, nullptr, nullptr};
@@ -1543,12 +1548,14 @@ sympix_status sympix_sample_BtNB_cross(const sympix_cross *c, const sympix_kerne
     sympix::BtnbArgs a;
     a.u64t = b->u64t;
     a.ut32 = b->ut32;
+    a.masks = b->masks;
     a.classes = dx->classes;
     a.class_terms = dx->class_terms;
     a.class_blk = dx->class_blk;
     a.class_itab = dx->class_itab;
     a.mtiles = dx->gtiles;
     a.nmtiles = (int64_t)x.cls.gtiles.size() / 4;
+    a.max_terms = x.cls.max_class_terms;
     a.nblocks = nblocks;
     a.npix = g2.npix;
     a.ninv = ninv2_dev;

@@ -34,6 +34,17 @@ struct KTable {
     double y_cut;         // values at y > y_cut are 0 (+inf: no cut)
 };
 
+// Where a kernel's unique blocks are zero (the radial cut): per block and
+// column q the units, four columns of a ring of tile I, that are not all zero
+// (bit 8 h + r: ring r, columns 4 h .. 4 h + 3, i.e. rows p = 32 h + 8 l + r,
+// l = 0 .. 3), the same of each group of 16 columns, and whether any element
+// of any block is not finite (a table that overflowed).
+struct UnitMasks {
+    uint16_t *units;      // [nunique][64]
+    uint16_t *cols;       // [nunique][4]
+    int32_t *overflow;
+};
+
 constexpr int kBlockDim = 64;              // k^2 for k = 8
 constexpr int kBlockElems = 64 * 64;
 constexpr int kMaxClassTerms = 128;     // contraction terms a class may have (two-grid blocks have up to ~4x
@@ -42,14 +53,16 @@ constexpr int kTileStride = kMaxClassTerms + 1;   // LDS row stride of the membe
                                                   // conflicts when the lanes of a wave read 16 rows)
 
 // a6: table of sum_l c_l P_l(1 - s^2), c_l = (2l+1) coef_l / 4 pi
+// (and clears *overflow)
 hipError_t launch_tabulate(const double *coef, int32_t lmax, double h, double *table,
-                           int32_t n_nodes, hipStream_t st);
+                           int32_t n_nodes, int32_t *overflow, hipStream_t st);
 // evaluation of the table at arbitrary y (tests of the interpolation)
 hipError_t launch_eval(KTable kt, const double *y, double *out, int64_t n, hipStream_t st);
 // a7: every unique block, FP64 row-major [uid][p][q] plus FP64 and FP32
-// copies transposed [uid][q][p]
+// copies transposed [uid][q][p], and their unit masks
 hipError_t launch_unique_eval(KTable kt, const UInfo *uinfo, int64_t nunique, const double *ring_theta,
-                              const double *ring_sin, double *u64, double *u64t, float *ut32, hipStream_t st);
+                              const double *ring_sin, double *u64, double *u64t, float *ut32, const UnitMasks &um,
+                              hipStream_t st);
 // a8: D-hat expansion: each work item {uid, first, count, 0} copies unique
 // block uid into the stored blocks exp_blk[first .. first + count)
 hipError_t launch_expand(const double *u64, const int32_t *items, int64_t nitems, const int32_t *exp_blk,
@@ -71,6 +84,8 @@ struct BtnbArgs {
     int64_t nblocks;
     const double *ninv;
     double *out;
+    UnitMasks masks;          // of the unique blocks u64t / ut32
+    int32_t max_terms;        // most terms of a class
     // optional D-hat blocks written by the same launch:
     // stored block n gets unique block blk_uid[n] of du64 (row-major FP64)
     const double *du64;
@@ -90,6 +105,9 @@ struct ProblemDesc64 {
     const double *du64;       // D-hat: unique blocks, row-major FP64 (with outD)
     const int32_t *blk_uid;   // unique block of each stored block
     double *outD;             // D-hat output, or nullptr
+    const uint16_t *units, *unit_cols;   // UnitMasks of u64t
+    const int32_t *overflow;
+    int32_t max_terms;        // most terms a class of the launch has
 };
 
 // Operands of the split-BF16 class GEMM (device pointers).
@@ -148,6 +166,7 @@ struct BatchLaunch {
     int32_t *counters;        // nq
     bool persistent;          // false: one class-GEMM launch per problem
     int32_t nworkgroups;
+    int32_t max_terms;        // most terms of a class of any problem
 };
 hipError_t launch_batch(const BatchLaunch &b, hipStream_t st);
 
@@ -158,6 +177,7 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t st);
 constexpr int64_t kNoAllocMaxPix = int64_t(1) << 24;
 constexpr int kNoAllocMaxDevices = 64;
 hipError_t noalloc_scratch(int device, void **ptr);
-hipError_t batch_occupancy(int prec, int *workgroups_per_cu);
+// readies the batch kernel of a mode for classes of up to max_terms terms and returns how many of its workgroups share a CU
+hipError_t batch_prepare(int prec, int max_terms, int *workgroups_per_cu);
 
 }  // namespace sympix

@@ -55,7 +55,8 @@ __device__ __forceinline__ int xcd_contiguous_index() {
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_tabulate(const double *__restrict__ coef, int lmax,
                                                   double h, double *__restrict__ table,
-                                                  int n_nodes) {
+                                                  int n_nodes, int32_t *__restrict__ overflow) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *overflow = 0;   // set by k_unique_eval, next on the stream
     // Per-degree factors of the recurrence, staged in LDS a chunk of degrees
     // at a time by the whole workgroup: step l takes d <- A_l d - B_l y p with
     // A_l = l / (l + 1), B_l = (2l + 1) / (l + 1), then p <- p + d (now
@@ -130,8 +131,10 @@ __global__ __launch_bounds__(256) void k_unique_eval(KTable kt, const UInfo *__r
                                                      const double *__restrict__ ring_sin,
                                                      double *__restrict__ u64,
                                                      double *__restrict__ u64t,
-                                                     float *__restrict__ ut32) {
+                                                     float *__restrict__ ut32, UnitMasks um) {
     __shared__ double tile[64][65];
+    __shared__ uint32_t scols[4];
+    if (threadIdx.x < 4) scols[threadIdx.x] = 0;
     const int64_t uid = blockIdx.x;
     const UInfo inf = uinfo[uid];
     const int64_t M = (int64_t)inf.n_i * inf.n_j;
@@ -159,7 +162,21 @@ __global__ __launch_bounds__(256) void k_unique_eval(KTable kt, const UInfo *__r
         const double v = tile[p][q];
         u64t[base + e] = v;
         ut32[base + e] = (float)v;
+        // rings of each half of the tile (four columns) that are not all zero in column q
+        const uint64_t nzp = __ballot(v != 0.0);
+        uint32_t lo = (uint32_t)nzp, hi = (uint32_t)(nzp >> 32);
+        lo |= lo >> 16;
+        hi |= hi >> 16;
+        const uint32_t nz = ((lo | lo >> 8) & 255u) | ((hi | hi >> 8) & 255u) << 8;
+        const bool over = __any(!(fabs(v) < INFINITY));
+        if (p == 0) {
+            um.units[uid * 64 + q] = (uint16_t)nz;
+            atomicOr(&scols[q >> 4], nz);
+            if (over) atomicOr(um.overflow, 1);
+        }
     }
+    __syncthreads();
+    if (threadIdx.x < 4) um.cols[uid * 4 + threadIdx.x] = (uint16_t)scols[threadIdx.x];
 }
 
 // ---------------------------------------------------------------------------
@@ -285,24 +302,29 @@ __global__ __launch_bounds__(256) void k_convolve(const double *__restrict__ u64
 // (the combined call): each stored block gets its unique D-hat block
 // (row-major FP64).  Chunk c of a tile is 16 bytes (c & 2047) of member row
 // c >> 11; a wave's 64 chunks lie in one row, so the row is uniform.  Step stp
-// of a workgroup of NT threads loads chunks [2 NT stp, 2 NT (stp + 1)), two per
+// of a workgroup of NT threads loads chunks [N NT stp, N NT (stp + 1)), N per
 // thread; they are stored one step later, right after that step's loads:
 // stores and loads share one wait counter, and a store placed there is waited
 // for only by the next step's operand wait.  sBlk[m] is the stored block of
 // member row m (-1: none), sBlk[64 + m] its unique D-hat block.
 // ---------------------------------------------------------------------------
+template <int N>
 struct DCopy {
-    doublex2 v[2];
-    double *dst[2];            // uniform: where the chunk row goes (nullptr: nowhere)
+    doublex2 v[N];
+    double *dst[N];            // uniform: where the chunk row goes (nullptr: nowhere)
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int r = 0; r < N; ++r) dst[r] = nullptr;
+    }
 };
 
-template <int NT>
+template <int NT, int N>
 __device__ __forceinline__ void dcopy_load(const double *__restrict__ du64, double *__restrict__ outD,
                                            const int32_t *sBlk, int nchunks, int stp, int wave, int lane,
-                                           DCopy &dc) {
+                                           DCopy<N> &dc) {
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int c0 = __builtin_amdgcn_readfirstlane((2 * stp + r) * NT + 64 * wave);
+    for (int r = 0; r < N; ++r) {
+        const int c0 = __builtin_amdgcn_readfirstlane((N * stp + r) * NT + 64 * wave);
         const bool ok = c0 < nchunks;
         const int m = ok ? c0 >> 11 : 0;
         const int blk = __builtin_amdgcn_readfirstlane(sBlk[m]);
@@ -314,9 +336,10 @@ __device__ __forceinline__ void dcopy_load(const double *__restrict__ du64, doub
     }
 }
 
-__device__ __forceinline__ void dcopy_store(const DCopy &dc, int lane) {
+template <int N>
+__device__ __forceinline__ void dcopy_store(const DCopy<N> &dc, int lane) {
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+    for (int r = 0; r < N; ++r)
         if (dc.dst[r]) __builtin_nontemporal_store(dc.v[r], (doublex2 *)(dc.dst[r] + 2 * lane));
 }
 
@@ -345,12 +368,36 @@ __device__ __forceinline__ void empty_class_tile(const PD &pd, const DevClass &c
 // a9, FP64 MFMA class GEMM (the class decomposition is described with the
 // FP32 form below).  W = N^-1 as given, M = B_IJ[p][a] B_IK[p][b] formed in
 // FP64 from the transposed FP64 unique blocks.  MFMA 16x16x4 FP64: lane
-// (lr, lk) holds W[16 i + lr][p] and M[p][16 j + lr] for p = 16 g + 4 lk + t;
-// its result holds members 16 i + lk + 4 v of column b = 16 j + lr.  The MFMA
-// accumulates in FP64 across all terms of an output row, so there is no
-// separate accumulation step; four waves share a member tile and take every
-// fourth row a; each step (16 pixels of one term) loads the next step's
-// operands before its own MFMAs.
+// (lr, lk) holds W[16 i + lr][p] and M[p][16 j + lr], its result members 16 i +
+// lk + 4 v of column b = 16 j + lr.  The MFMA accumulates in FP64 across all
+// terms of an output row, so there is no separate accumulation step.
+//
+// Blocks cut at a radius are largely zero: a 3-pixel beam cut at three FWHM
+// leaves 44% of the elements of the unique blocks, and 27% of the products
+// B[p][a] B[p][b] of a contraction.  So only products that can be nonzero are
+// formed, in whole MFMAs.  An MFMA's four pixels are a unit, four columns of
+// one ring of the tile (pixel lk of the unit at lane lk), and bit masks written
+// with the unique blocks say in which units a column a, or a group of 16
+// columns, is not all zero.  A step is one term's group of 4 x 4 pixels (MFMA t
+// takes its ring t), the four waves of a workgroup take R consecutive rows a
+// through the same steps, listed beforehand (those in which any of the rows and
+// any column can be nonzero), and each wave runs only the MFMAs whose row and
+// column group are not all zero in unit t.  What is left out are products with
+// an exact zero, so the sums are those of the full contraction bit for bit,
+// whatever rows and members share a tile.  A tile whose N^-1 holds an infinity
+// or NaN, and a kernel whose table overflowed, run the full lists, since there
+// a zero factor does not give a zero product.  MFMAs left (lmax 256, beam 3
+// pixels): 48%; units of four rings of a column would leave 55%.
+//
+// The operands of a step are staged through LDS for all four waves (W of the
+// tile's rows, the B_IK values of all columns, the B_IJ values of the rows), by
+// loads that write LDS directly, three steps ahead into three buffers, one
+// barrier per step.  With so few MFMAs per step, operands loaded by each wave on
+// its own were bound by L2 (16 bytes per clock and CU).  Wave w takes column
+// group (w + r) mod 4 of row r: 16 accumulators, so that two workgroups share a
+// CU (one's MFMAs run while the other waits or stores), and the four waves'
+// shares of a step are nearly equal (one column group per wave: the longest of
+// the four is 11% above their mean, one row per wave 18%, this 1%).
 //
 // Symmetric classes (every term pairs a unique block with itself: the blocks
 // (J, J)) give C[a][b] = C[b][a] bit for bit, since the products B[p][a]
@@ -359,233 +406,423 @@ __device__ __forceinline__ void empty_class_tile(const PD &pd, const DevClass &c
 // tiles below the diagonal as mirror images (plain stores: a mirrored row
 // gets its 16 values from 16 rows a at different times, and L2 merges them,
 // where streaming stores would send each 8 bytes out as a partial line).
-// Wave w's row x is a = w + 4 x,
-// so a / 16 = x / 4: its rows run in four phases with the first column group
-// JLO fixed at compile time (JLO = 0 for every row of other classes).  A step
-// issues one W load per 16 members whatever the number of column groups, so
-// the later phases take R rows a, a + 4, ... at once (R NI (4 - JLO) <= 16
-// accumulators), sharing the W and M-column loads between them: every step
-// keeps 64 MFMAs in a full tile.
+// There wave w takes row w of every four, with all column groups it needs: the
+// rows run in four phases whose first column group JLO is a compile-time
+// constant, and a step takes more rows the fewer column groups they have.
+// Measured (MI355X, beam 3 pixels; the full contraction in 4-wave workgroups,
+// operands loaded per wave, before): contraction alone 46.1 -> 26.8 ms at lmax
+// 3000 and 12.0 -> 6.8 ms at 1500, with D-hat 48.1 -> 29.3 ms at lmax 3000; the
+// MFMAs left take 18 ms at the FP64 matrix rate.  Beam 2 pixels (lmax 2048):
+// 23.5 -> 6.6 ms, 5 pixels (91% of the MFMAs left): 23.6 -> 21.8 ms.
 // ---------------------------------------------------------------------------
-template <int NI, int JLO>
-struct F64Phase {
-    static constexpr int NJ = 4 - JLO;
-    static constexpr int R = 4 * NI * NJ <= 16 ? 4 : 2 * NI * NJ <= 16 ? 2 : 1;
-    static_assert(R * NI * NJ <= 16, "a phase holds at most 16 accumulators");
+// Rows per row group and of them per wave: R rows by all waves, or in phase JLO
+// of a symmetric class 4 f64_sym_rows, one in four per wave: as many as keep 16
+// accumulators busy (and lie in the phase).
+__host__ __device__ constexpr int f64_rows(int ni) { return ni == 4 ? 4 : 8; }
+__host__ __device__ constexpr int f64_sym_rows(int ni, int jlo) { return jlo == 3 ? 4 : jlo == 2 ? (ni == 4 ? 2 : 4) : ni == 4 ? 1 : 2; }
+constexpr int kLastStep = 0x8000;
+
+// LDS of an FP64 class tile, sized by the most terms S a class of the launch
+// has.  The staging buffers come first: three of kStage bytes, holding W (64
+// rows of 128 bytes), B_IK (64 columns) and B_IJ (16 rows).
+constexpr int kStageU2 = 64 * 128, kStageU1 = 2 * 64 * 128, kStage = kStageU1 + 16 * 128;
+
+struct F64Lds {
+    char *stage;
+    int32_t *blk;               // [192]: stored block per member row; its D-hat source block; and the stored
+                                // blocks again, at 16 i + 4 lk + v that of row 16 i + lk + 4 v
+    int32_t *bad;               // N^-1 of the tile holds a value that is not finite
+    uint16_t *mask;             // [64 * S]: units of (term, row a) in which B_IJ is not all zero
+    uint16_t *cols;             // [4 * S]: units of (term, column group j) in which B_IK is not all zero
+    uint32_t *on;               // [4][3][4 * S]: per wave, steps of three row groups: bit 4 q + t for MFMA t of accumulator q
+    uint16_t *code;             // [4][3][4 * S]: 4 term + pixel group of these steps, the last with kLastStep
+    int32_t *term;              // [2 * S]: unique-block pairs of the class
+    int32_t *tile;              // [64 * stride]: tile I of (member row, term)
+    int stride, terms;          // terms: S
 };
 
+__host__ __device__ constexpr int f64_lds_bytes(int S) {
+    return 3 * kStage + 4 * (192 + 8) + 2 * (64 + 4 + 48) * S + 4 * (48 * S + 2 * S + 64 * (S | 1));
+}
+
+__device__ __forceinline__ F64Lds f64_lds(char *p, int S) {
+    F64Lds l;
+    l.stage = p;
+    l.blk = (int32_t *)(p + 3 * kStage);
+    l.bad = l.blk + 192;
+    l.mask = (uint16_t *)(l.bad + 8);          // 8-byte aligned, as cols: read four at a time
+    l.cols = l.mask + 64 * S;
+    l.code = l.cols + 4 * S;
+    l.term = (int32_t *)(l.code + 48 * S);
+    l.on = (uint32_t *)(l.term + 2 * S);
+    l.tile = (int32_t *)(l.on + 48 * S);
+    l.terms = S;
+    l.stride = S | 1;                        // odd: rows fall on different banks
+    return l;
+}
+
+// One 16-byte load per lane straight into LDS: lane l's value goes to byte lds +
+// 16 l (uniform lds).  Counted in vmcnt; the compiler knows of neither, so the
+// waits are written out where the staged data change hands.
+__device__ __forceinline__ void load_to_lds(const void *src, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(src) : "memory");
+}
+// The same with a uniform address and a byte offset per lane.
+__device__ __forceinline__ void load_to_lds(const void *uniform_src, uint32_t offset, uint32_t lds) {
+    const uint64_t p = (uint64_t)(uintptr_t)uniform_src;
+    const uint64_t src = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)p) |
+                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(p >> 32)) << 32;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(offset), "s"(src) : "memory");
+}
+
+// Every load but the N youngest memory operations done, and LDS traffic too;
+// then the workgroup's barrier.
+template <int N>
+__device__ __forceinline__ void wait_and_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+__device__ __forceinline__ bool not_finite(double v) {
+    return ((uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32) & 0x7ff00000u) == 0x7ff00000u;
+}
+
 template <int NI, bool WD>
-__device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item, int32_t *sTile,
-                                               int32_t *sBlk, int32_t *sTerm) {
+__device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item, int part, int parts, const F64Lds &lds) {
+    constexpr int R = f64_rows(NI);
     const double *__restrict__ ut = pd.u64t;
     const double *__restrict__ wv = pd.w;
     double *__restrict__ out = pd.out;
     const int cls = pd.mtiles[4 * item], m0 = pd.mtiles[4 * item + 1];
     const DevClass cl = pd.classes[cls];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, lr = lane & 15, lk = lane >> 4;
     const int nterms = cl.nterms;
     const int32_t *terms = pd.cterms + 2 * cl.term0;
     if (nterms == 0) {
-        empty_class_tile<256, WD>(pd, cl, m0, 16 * NI);
+        if (part == 0) empty_class_tile<256, WD>(pd, cl, m0, 16 * NI);
         return;
     }
 
-    for (int x = threadIdx.x; x < 16 * NI * nterms; x += 256) {
+    for (int x = tid; x < 16 * NI * nterms; x += 256) {
         const int r = x / nterms, e = x - r * nterms;
         const int m = min(m0 + r, cl.nblocks - 1);   // rows past the class repeat its last member
-        sTile[r * kTileStride + e] = pd.citab[cl.itab0 + (int64_t)m * nterms + e];
+        lds.tile[r * lds.stride + e] = pd.citab[cl.itab0 + (int64_t)m * nterms + e];
     }
-    if (threadIdx.x < 64) {
+    if (tid < 64) {
         const int blk = lane < 16 * NI && m0 + lane < cl.nblocks ? pd.cblk[cl.blk0 + m0 + lane] : -1;
-        sBlk[lane] = blk;
-        if constexpr (WD) sBlk[64 + lane] = blk >= 0 ? pd.blk_uid[blk] : 0;   // D-hat source block
+        lds.blk[lane] = blk;
+        lds.blk[128 + (lane & 48) + 4 * (lane & 3) + (lane >> 2 & 3)] = blk;
+        if constexpr (WD) lds.blk[64 + lane] = blk >= 0 ? pd.blk_uid[blk] : 0;   // D-hat source block
     }
-    if (threadIdx.x < 2 * nterms) sTerm[threadIdx.x] = terms[threadIdx.x];   // unique-block pairs of the class
+    for (int x = tid; x < 2 * nterms; x += 256) lds.term[x] = terms[x];
+    for (int x = tid; x < 32 * nterms; x += 256)                           // 64 masks of 2 bytes per term
+        ((uint32_t *)lds.mask)[x] = ((const uint32_t *)pd.units)[(int64_t)terms[2 * (x >> 5)] * 32 + (x & 31)];
+    for (int x = tid; x < 4 * nterms; x += 256)
+        lds.cols[x] = pd.unit_cols[(int64_t)terms[2 * (x >> 2) + 1] * 4 + (x & 3)];
+    if (tid == 0) *lds.bad = *pd.overflow;
     __syncthreads();
+    bool bad = false;                    // sixteen threads per (member row, term), four pixels each
+    for (int r = tid >> 4; r < 16 * NI; r += 16)
+        for (int e = 0; e < nterms; ++e) {
+            const doublex4 v = *(const doublex4 *)(wv + (int64_t)lds.tile[r * lds.stride + e] * 64 + 4 * lr);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) bad |= not_finite(v[t]);
+        }
+    if (bad) *lds.bad = 1;
+    __syncthreads();
+    if (*lds.bad != 0) {
+        for (int x = tid; x < 32 * nterms; x += 256) ((uint32_t *)lds.mask)[x] = 0xffffffffu;
+        for (int x = tid; x < 2 * nterms; x += 256) ((uint32_t *)lds.cols)[x] = 0xffffffffu;
+        __syncthreads();
+    }
 
-    // operand pointers of term e for the row group starting at row a (rows
-    // a + 4 r of the group lie 256 r further along u1)
-    struct Ptrs { const double *w[NI], *u1, *u2; };
-    auto ptrs = [&](int a, int e, Ptrs &q) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-            q.w[i] = wv + (int64_t)sTile[(16 * i + lr) * kTileStride + e] * 64 + 4 * lk;
-        q.u1 = ut + (int64_t)__builtin_amdgcn_readfirstlane(sTerm[2 * e]) * kBlockElems + a * 64 + 4 * lk;
-        q.u2 = ut + (int64_t)__builtin_amdgcn_readfirstlane(sTerm[2 * e + 1]) * kBlockElems + lr * 64 + 4 * lk;
+    // Row groups: R rows each, or the phases of a symmetric class one after the
+    // other (phase p in groups of 4 f64_sym_rows rows, from group first[p] on).
+    constexpr int kRows[4] = {4 * f64_sym_rows(NI, 0), 4 * f64_sym_rows(NI, 1), 4 * f64_sym_rows(NI, 2), 4 * f64_sym_rows(NI, 3)};
+    constexpr int kFirst[5] = {0, 16 / kRows[0], 16 / kRows[0] + 16 / kRows[1], 16 / kRows[0] + 16 / kRows[1] + 16 / kRows[2],
+                               16 / kRows[0] + 16 / kRows[1] + 16 / kRows[2] + 16 / kRows[3]};
+    const bool sym = cl.sym != 0;
+    auto phase_of = [&](int g) { return !sym || g < kFirst[1] ? 0 : g < kFirst[2] ? 1 : g < kFirst[3] ? 2 : 3; };
+    auto rows_of = [&](int g) { const int p = phase_of(g); return !sym ? R : p == 0 ? kRows[0] : p == 1 ? kRows[1] : p == 2 ? kRows[2] : kRows[3]; };
+    auto row0_of = [&](int g) {
+        const int p = phase_of(g);
+        return !sym ? R * g : 16 * p + rows_of(g) * (g - (p == 0 ? 0 : p == 1 ? kFirst[1] : p == 2 ? kFirst[2] : kFirst[3]));
     };
-    struct Frag { doublex4 w[NI], u1[4], u2[4]; };
-    // operands of pixel group g in the shape of phase JL (its R rows, its
-    // column groups >= JL)
-    auto load = [&](auto jt, const Ptrs &q, int g, Frag &f) {
-        constexpr int JL = decltype(jt)::value, RL = F64Phase<NI, JL>::R;
+    const int ng = sym ? kFirst[4] : 64 / R;
+    parts = min(parts, ng);
+    if (part >= parts) return;
+    const int g_begin = ng * part / parts, g_end = ng * (part + 1) / parts;   // this workgroup's groups
+
+    // The steps of row group g, and this wave's MFMAs of them, into its lists:
+    // lane 4 e + G looks at pixel group G of term e.  Every wave builds its own
+    // (the steps are the same for all).  At least two steps: the first pixel group
+    // left out fills up, with no MFMA.
+    auto build = [&](int g) __attribute__((always_inline)) {
+        uint16_t *code = lds.code + (3 * wave + g % 3) * 4 * lds.terms;
+        uint32_t *on = lds.on + (3 * wave + g % 3) * 4 * lds.terms;
+        const int a0 = row0_of(g), nr = rows_of(g), jlo = phase_of(g);
+        int n = 0, spare = 0;
+        for (int e0 = 0; e0 < nterms; e0 += 16) {
+            const int e = min(e0 + (lane >> 2), nterms - 1), G = lane & 3;
+            const bool ok = e0 + (lane >> 2) < nterms;
+            // bits 16 j + t of c: column group j; bits 16 r + t of m: row r of four
+            const uint64_t nib = 0x000f000f000f000full;
+            uint64_t c = *(const uint64_t *)(lds.cols + 4 * e) >> (4 * G) & nib;
+            if (jlo > 0) c = c >> (16 * jlo) << (16 * jlo);
+            uint32_t any_c = (uint32_t)c | (uint32_t)(c >> 32), bits = 0, any_m = 0;
+            any_c |= any_c >> 16;
+            if (!sym) {
+                if (wave != 0) c = c >> (16 * wave) | c << (64 - 16 * wave);   // column group (w + r) mod 4 to place r
 #pragma unroll
-        for (int i = 0; i < NI; ++i) f.w[i] = *(const doublex4 *)(q.w[i] + 16 * g);
-#pragma unroll
-        for (int r = 0; r < RL; ++r) f.u1[r] = *(const doublex4 *)(q.u1 + 256 * r + 16 * g);
-#pragma unroll
-        for (int j = JL; j < 4; ++j) f.u2[j] = *(const doublex4 *)(q.u2 + 16 * j * 64 + 16 * g);
+                for (int r = 0; r < R; r += 4) {
+                    const uint64_t m = *(const uint64_t *)(lds.mask + 64 * e + a0 + r) >> (4 * G) & nib, x = m & c;
+                    any_m |= (uint32_t)m | (uint32_t)(m >> 32);
+                    const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
+                    bits |= ((lo | lo >> 12) & 255u | ((hi | hi >> 12) & 255u) << 8) << (4 * r);
+                }
+            } else {
+                const int nj = 4 - jlo;
+                for (int r = 0; r < nr; r += 4) {
+                    const uint64_t m = *(const uint64_t *)(lds.mask + 64 * e + a0 + r) >> (4 * G) & nib;
+                    any_m |= (uint32_t)m | (uint32_t)(m >> 32);
+                    const uint32_t own = (uint32_t)(m >> (16 * wave)) & 15u;
+                    for (int j = jlo; j < 4; ++j) bits |= (own & (uint32_t)(c >> (16 * j))) << (4 * (r / 4 * nj + j - jlo));
+                }
+            }
+            any_m |= any_m >> 16;
+            const bool any = (any_m & any_c & 15u) != 0;
+            const uint64_t in_b = __ballot(ok && any), out_b = __ballot(ok && !any);
+            if (ok && any) {
+                const int i = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(in_b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in_b, 0));
+                code[i] = (uint16_t)(4 * e + G);
+                on[i] = bits;
+            }
+            n += __popcll(in_b);
+            if (out_b) spare = 4 * e0 + (__ffsll((unsigned long long)out_b) - 1);
+        }
+        if (lane < 2 - n) {
+            code[n + lane] = (uint16_t)spare;
+            on[n + lane] = 0;
+        }
+        // read by other lanes of this wave
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (lane == 0) code[max(n, 2) - 1] |= kLastStep;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
 
-    // accumulator of (row r of the group, member group i, column group j) in
-    // phase JLO; every slot is zero between row groups
-    doublex4 acc[16];
-#pragma unroll
-    for (int s = 0; s < 16; ++s) acc[s] = doublex4{0.0, 0.0, 0.0, 0.0};
+    // Staging of one step, 16 bytes per lane and load: row r (a member row of W,
+    // a column of B_IK, a row of B_IJ) keeps its 16-byte chunk c (pixels 8 (c /
+    // 2) + 2 (c mod 2) and the next of the group's) at 8 r + (c ^ (r & 7)), so
+    // that the eight lanes of a read phase fall on different banks.  Wave w
+    // loads rows 16 w + 8 k + lane / 8 (k = 0, 1) of W and B_IK, and half of the
+    // rows of B_IJ.  Rows past the tile repeat its last member, rows past the
+    // group its own (no wave reads them).
+    const int lrow = lane >> 3, lchunk = (lane & 7) ^ lrow;
+    const int lpix = 8 * (lchunk >> 1) + 2 * (lchunk & 1);
+    const int wrow0 = min(16 * wave + lrow, 16 * NI - 1) * lds.stride;
+    const int wrow1 = min(16 * wave + 8 + lrow, 16 * NI - 1) * lds.stride;
+    const uint32_t stage0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds.stage;
+    constexpr int kLoads = 5;            // per wave and step
+    // where a step (g, code) finds its operands: its term's unique blocks, and this lane's tiles I
+    struct Src { int g, code, tile0, tile1, uid1, uid2; };
+    auto source = [&](int g, int code) __attribute__((always_inline)) {
+        const int e = (code & ~kLastStep) >> 2;
+        return Src{g, code, lds.tile[wrow0 + e], lds.tile[wrow1 + e], lds.term[2 * e], lds.term[2 * e + 1]};
+    };
+    const uint32_t off2 = 8 * (lrow * 64 + lpix);                     // lane offsets into B_IK and B_IJ
+    const uint32_t off1 = 8 * (((8 * (wave & 1) + lrow) & (R - 1)) * 64 + lpix);
+    struct Addr { const double *w0, *w1, *u2, *u1; uint32_t off1; };
+    auto addresses = [&](const Src &q) __attribute__((always_inline)) {
+        const int pix = 32 * (q.code >> 1 & 1) + 4 * (q.code & 1);
+        const double *w = wv + pix;
+        return Addr{w + ((int64_t)q.tile0 * 64 + lpix), w + ((int64_t)q.tile1 * 64 + lpix),
+                    ut + (int64_t)__builtin_amdgcn_readfirstlane(q.uid2) * kBlockElems + (16 * wave * 64 + pix),
+                    ut + (int64_t)__builtin_amdgcn_readfirstlane(q.uid1) * kBlockElems + (row0_of(q.g) * 64 + pix),
+                    sym ? 8 * (((8 * (wave & 1) + lrow) & (rows_of(q.g) - 1)) * 64 + lpix) : off1};
+    };
+    auto stage = [&](const Addr &q, uint32_t at) __attribute__((always_inline)) {
+        load_to_lds(q.w0, at + 2048 * wave);
+        load_to_lds(q.w1, at + 2048 * wave + 1024);
+        load_to_lds(q.u2, off2, at + kStageU2 + 2048 * wave);
+        load_to_lds(q.u2 + 8 * 64, off2, at + kStageU2 + 2048 * wave + 1024);
+        load_to_lds(q.u1, q.off1, at + kStageU1 + 1024 * (wave & 1));   // two waves write the same
+    };
+    // pixels 8 lk + 2 h, 8 lk + 2 h + 1 of a staged row
+    auto staged = [&](const char *rows, int r, int h) __attribute__((always_inline)) {
+        return *(const doublex2 *)(rows + 128 * r + 16 * ((2 * lk + h) ^ (r & 7)));
+    };
+
+    // Steps in order: step s of group g with code c is followed by step s + 1, or
+    // if it is the last by the next group's first; past the last group it
+    // repeats (its loads go where no step reads).
+    struct Cursor { int g, s; };
+    auto after = [&](const Cursor &c, int code) __attribute__((always_inline)) {
+        return !(code & kLastStep) ? Cursor{c.g, c.s + 1} : c.g + 1 < g_end ? Cursor{c.g + 1, 0} : c;
+    };
+    auto code_at = [&](const Cursor &c) __attribute__((always_inline)) { return (int)lds.code[(3 * wave + c.g % 3) * 4 * lds.terms + c.s]; };
+    auto on_at = [&](const Cursor &c) __attribute__((always_inline)) { return (int)lds.on[(3 * wave + c.g % 3) * 4 * lds.terms + c.s]; };
+    auto uniform = [&](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
+
     constexpr int kDChunks = 16 * NI * 2048;   // D-hat chunks of the tile
-    // One step of phase JLO: the loads of the next step in the shape of phase
-    // JN (JLO itself, or the next phase for the last step of a phase), then
-    // this step's products and MFMAs.
-    auto step = [&](auto jt, auto jn, const Frag &f, const Ptrs &qn, int gn, Frag &fn, int stp, DCopy &dprev) {
-        constexpr int JLO = decltype(jt)::value, NJ = F64Phase<NI, JLO>::NJ, R = F64Phase<NI, JLO>::R;
-        constexpr int JN = decltype(jn)::value;
-        constexpr int NLOAD = 2 * (NI + F64Phase<NI, JN>::R + F64Phase<NI, JN>::NJ);
-        load(jn, qn, gn, fn);
-        if constexpr (WD) {
-            DCopy dc;
-            dcopy_load<256>(pd.du64, pd.outD, sBlk, kDChunks, stp, wave, lane, dc);
-            dcopy_store(dprev, lane);
-            dprev = dc;
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            double bv[4][4];
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int j = JLO; j < 4; ++j) bv[r][j] = f.u1[r][t] * f.u2[j][t];
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int i = 0; i < NI; ++i)
-#pragma unroll
-                    for (int j = JLO; j < 4; ++j) {
-                        doublex4 &c = acc[(r * NJ + j - JLO) * NI + i];
-                        c = __builtin_amdgcn_mfma_f64_16x16x4f64(f.w[i][t], bv[r][j], c, 0, 0, 0);
-                    }
-        }
-        __builtin_amdgcn_sched_group_barrier(0x020, NLOAD, 0);          // loads first
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            __builtin_amdgcn_sched_group_barrier(0x002, R * NJ, 0);      // products of pixel t
-            __builtin_amdgcn_sched_group_barrier(0x008, R * NJ * NI, 0); // their MFMAs
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    // end of a row group (first row x): store groups >= JLO of its rows (and
-    // their mirror images below the diagonal in a symmetric class), clear
-    auto store_group = [&](auto jt, auto symt, int x) {
-        constexpr int JLO = decltype(jt)::value, NJ = F64Phase<NI, JLO>::NJ, R = F64Phase<NI, JLO>::R;
+    int stp = kDChunks / 512 * part / parts;   // steps done, counted from the first of this part's chunks
+    const int dchunks = kDChunks / 512 * (part + 1) / parts * 512;
+    DCopy<2> dpend;
+    for (int g = g_begin; g < min(g_begin + 2, g_end); ++g) build(g);
+    int code0, code1, code2, code3;
+    uint32_t on;                         // on: this wave's MFMAs of this step
+    Cursor c1, c2, c3;                   // the next three steps
+    {
+        const Cursor c0{g_begin, 0};
+        code0 = uniform(code_at(c0));
+        on = uniform(on_at(c0));
+        c1 = after(c0, code0);
+        code1 = uniform(code_at(c1));
+        if (g_begin + 2 < g_end) build(g_begin + 2);
+        c2 = after(c1, code1);
+        code2 = uniform(code_at(c2));
+        c3 = after(c2, code2);
+        code3 = uniform(code_at(c3));
+        stage(addresses(source(c0.g, code0)), stage0);
+        stage(addresses(source(c1.g, code1)), stage0 + kStage);
+        stage(addresses(source(c2.g, code2)), stage0 + 2 * kStage);
+    }
+    uint32_t at = 0;                     // this step's buffer
+    // The row groups [gb, ge) of this part.  SYM false: accumulator q is row q,
+    // column group (w + q) mod 4; SYM true: column groups >= JLO of the rows w, w + 4, ...
+    auto groups = [&](auto symt, auto jt, int gb, int ge) __attribute__((always_inline)) {
         constexpr bool SYM = decltype(symt)::value;
+        constexpr int JLO = decltype(jt)::value, NR = SYM ? f64_sym_rows(NI, JLO) : R, NJ = SYM ? 4 - JLO : 1;
+        auto row = [&](int q) { return SYM ? wave + 4 * (q / NJ) : q; };
+        auto col = [&](int q) { return SYM ? JLO + q % NJ : (wave + q) & 3; };
+        for (int g = max(gb, g_begin); g < min(ge, g_end); ++g) {
+            if (g > g_begin && g + 2 < g_end) build(g + 2);   // its place held group g - 1's
+            const int a0 = row0_of(g);
+            doublex4 acc[NR * NJ][NI];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int a = wave + 4 * (x + r);
+            for (int q = 0; q < NR * NJ; ++q)
+#pragma unroll
+                for (int i = 0; i < NI; ++i) acc[q][i] = doublex4{0.0, 0.0, 0.0, 0.0};
+            for (bool last = false; !last;) {
+                // read now, used after the MFMAs: what the loads of three steps on need, the code of the step
+                // after that, the next step's masks
+                const Src src = source(c3.g, code3);
+                const Cursor c4 = after(c3, code3);
+                const int code4 = code_at(c4);
+                const int on1 = on_at(c1);
+                if constexpr (WD) {
+                    dcopy_load<256>(pd.du64, pd.outD, lds.blk, dchunks, stp, wave, lane, dpend);
+                    ++stp;
+                }
+                const char *sw = lds.stage + at, *su2 = sw + kStageU2, *su1 = sw + kStageU1;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    constexpr int NC = SYM ? NJ : 4;
+                    doublex2 u1[NR], u2[NC], w[NI];
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) u1[r] = staged(su1, row(r * NJ), h);
+#pragma unroll
+                    for (int j = 0; j < NC; ++j) u2[j] = staged(su2, 16 * (SYM ? JLO + j : (wave + j) & 3) + lr, h);
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) w[i] = staged(sw, 16 * i + lr, h);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int q = 0; q < NR * NJ; ++q)
+                            if (on & (1u << (4 * q + 2 * h + t))) {
+                                const double bv = u1[q / NJ][t] * u2[SYM ? q % NJ : q & 3][t];
+#pragma unroll
+                                for (int i = 0; i < NI; ++i)
+                                    acc[q][i] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[i][t], bv, acc[q][i], 0, 0, 0);
+                            }
+                }
+                const Addr ad = addresses(src);
+                last = (code0 & kLastStep) != 0;
+                c1 = c2;
+                c2 = c3;
+                c3 = c4;
+                code0 = code1;
+                code1 = code2;
+                code2 = code3;
+                code3 = uniform(code4);
+                on = uniform(on1);
+                // the next step's loads are done in every wave, and nobody reads this step's buffer any more
+                wait_and_barrier<kLoads + (WD ? 2 : 0)>();
+                if constexpr (WD) dcopy_store(dpend, lane);
+                stage(ad, stage0 + at);
+                at = at == 2 * kStage ? 0 : at + kStage;
+            }
+            // store the group's rows (and their mirror images below the diagonal in a symmetric class)
+            typedef int32_t intx4 __attribute__((ext_vector_type(4)));
+            intx4 blk[NI];
+#pragma unroll
+            for (int i = 0; i < NI; ++i) blk[i] = *(const intx4 *)(lds.blk + 128 + 16 * i + 4 * lk);
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int blk = sBlk[16 * i + lk + 4 * v];
-                    if (blk >= 0) {
-                        double *ob = out + (int64_t)blk * kBlockElems;
+                    if (blk[i][v] >= 0) {
+                        double *ob = out + (int64_t)blk[i][v] * kBlockElems;
 #pragma unroll
-                        for (int j = JLO; j < 4; ++j)
-                            __builtin_nontemporal_store(acc[(r * NJ + j - JLO) * NI + i][v], &ob[a * 64 + 16 * j + lr]);
-                        if constexpr (SYM) {
-#pragma unroll
-                            for (int j = JLO + 1; j < 4; ++j)
-                                ob[(16 * j + lr) * 64 + a] = acc[(r * NJ + j - JLO) * NI + i][v];
+                        for (int q = 0; q < NR * NJ; ++q) {
+                            const int a = a0 + row(q), b = 16 * col(q) + lr;
+                            __builtin_nontemporal_store(acc[q][i][v], &ob[a * 64 + b]);
+                            if (SYM && q % NJ > 0) ob[b * 64 + a] = acc[q][i][v];
                         }
                     }
                 }
         }
-#pragma unroll
-        for (int s = 0; s < R * NJ * NI; ++s) acc[s] = doublex4{0.0, 0.0, 0.0, 0.0};
-    };
-
-    Frag f0, f1;
-    Ptrs qc, qn;
-    int it = 0;                          // (row group, term) iterations done: 4 steps each
-    DCopy dpend;                         // D-hat chunks loaded, not yet stored
-    dpend.dst[0] = dpend.dst[1] = nullptr;
-    // rows x in [xb, xe) of phase JLO in groups of R; JN: the phase after it.
-    // One (row group x, term e) iteration is four steps; the last iteration of
-    // the phase is peeled, so that the operands it loads in the next phase's
-    // shape are live only from there on.
-    auto phase = [&](auto jt, auto jn, auto symt, int xb, int xe) {
-        constexpr int R = F64Phase<NI, decltype(jt)::value>::R;
-        auto iteration = [&](auto jl, int x, int e) {
-            const bool last_term = e + 1 == nterms;
-            const int nx = last_term ? x + R : x, ne = last_term ? 0 : e + 1;
-            if (nx < 16) ptrs(wave + 4 * nx, ne, qn);
-            else qn = qc;                // past the last row: a harmless reload
-            step(jt, jt, f0, qc, 1, f1, 4 * it, dpend);
-            step(jt, jt, f1, qc, 2, f0, 4 * it + 1, dpend);
-            step(jt, jt, f0, qc, 3, f1, 4 * it + 2, dpend);
-            step(jt, jl, f1, qn, 0, f0, 4 * it + 3, dpend);
-            if (last_term) store_group(jt, symt, x);
-            qc = qn;
-            ++it;
-        };
-        const int n_iter = (xe - xb) / R * nterms;
-        int x = xb, e = 0;
-        for (int n = 0; n + 1 < n_iter; ++n) {
-            iteration(jt, x, e);
-            if (++e == nterms) {
-                e = 0;
-                x += R;
-            }
-        }
-        iteration(jn, x, e);
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
     using I3 = std::integral_constant<int, 3>;
-    ptrs(wave, 0, qc);
-    load(I0(), qc, 0, f0);
-    if (cl.sym != 0) {
-        phase(I0(), I1(), std::true_type(), 0, 4);
-        phase(I1(), I2(), std::true_type(), 4, 8);
-        phase(I2(), I3(), std::true_type(), 8, 12);
-        phase(I3(), I3(), std::true_type(), 12, 16);
+    if (sym) {
+        wait_and_barrier<2 * kLoads>();
+        groups(std::true_type(), I0(), kFirst[0], kFirst[1]);
+        groups(std::true_type(), I1(), kFirst[1], kFirst[2]);
+        groups(std::true_type(), I2(), kFirst[2], kFirst[3]);
+        groups(std::true_type(), I3(), kFirst[3], kFirst[4]);
     } else {
-        phase(I0(), I0(), std::false_type(), 0, 16);
+        wait_and_barrier<2 * kLoads>();
+        groups(std::false_type(), I0(), 0, 64 / R);
     }
-    if constexpr (WD) {                  // the last step's chunks, then those past the last step
-        dcopy_store(dpend, lane);
-        for (int stp = 4 * it; 512 * stp < kDChunks; ++stp) {
-            DCopy dc;
-            dcopy_load<256>(pd.du64, pd.outD, sBlk, kDChunks, stp, wave, lane, dc);
+    wait_and_barrier<0>();               // no load into LDS outlives the tile
+    if constexpr (WD) {                  // the chunks past the last step
+        for (; 512 * stp < dchunks; ++stp) {
+            DCopy<2> dc;
+            dcopy_load<256>(pd.du64, pd.outD, lds.blk, dchunks, stp, wave, lane, dc);
             dcopy_store(dc, lane);
         }
     }
 }
 
 template <bool WD>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_class_f64(ProblemDesc64 pd) {
-    __shared__ int32_t sTile[64 * kTileStride];
-    __shared__ int32_t sBlk[128];                    // stored block per member row; D-hat source block
-    __shared__ int32_t sTerm[2 * kMaxClassTerms];     // unique-block pairs of the class
+    extern __shared__ __align__(16) char smem[];
+    const F64Lds lds = f64_lds(smem, pd.max_terms);
     const int item = blockIdx.x;        // pd.mtiles: a dispatch table, slot per workgroup
     const int groups = pd.mtiles[4 * item + 2];
     if (groups == 0) return;            // an empty slot
-    if (groups == 4) class_f64_tile<4, WD>(pd, item, sTile, sBlk, sTerm);
-    else if (groups == 2) class_f64_tile<2, WD>(pd, item, sTile, sBlk, sTerm);
-    else class_f64_tile<1, WD>(pd, item, sTile, sBlk, sTerm);
+    if (groups == 4) class_f64_tile<4, WD>(pd, item, blockIdx.y, gridDim.y, lds);
+    else if (groups == 2) class_f64_tile<2, WD>(pd, item, blockIdx.y, gridDim.y, lds);
+    else class_f64_tile<1, WD>(pd, item, blockIdx.y, gridDim.y, lds);
 }
 
 // Queue draining shared by the persistent batch kernels: thread 0 takes the
 // next item from queue home, then steals from the others in order; -1 once
-// every queue is empty.  Counters only grow, so every workgroup leaves.
+// every queue is empty.  Counters only grow, so every workgroup leaves.  Every
+// item is taken in `parts` parts: the result is parts times the item, plus the part.
 __device__ __forceinline__ int batch_next_item(const int32_t *__restrict__ qb, int32_t nq,
-                                               int32_t *__restrict__ counters, int home, int &tried) {
+                                               int32_t *__restrict__ counters, int home, int &tried, int parts = 1) {
     int it = -1;
     while (tried < nq) {
         const int q = (home + tried) % nq;
         const int c = atomicAdd(&counters[q], 1);
-        if (c < qb[q + 1] - qb[q]) {
-            it = qb[q] + c;
+        if (c < (qb[q + 1] - qb[q]) * parts) {
+            it = qb[q] * parts + c;
             break;
         }
         ++tried;
@@ -594,29 +831,30 @@ __device__ __forceinline__ int batch_next_item(const int32_t *__restrict__ qb, i
 }
 
 // a10 in FP64: the FP64 class GEMM of many problems in one persistent launch
-// (one 4-wave workgroup per CU, as k_class_f64), fed by the same queues as the
+// (two 4-wave workgroups per CU, as k_class_f64), fed by the same queues as the
 // FP32 and split-BF16 batch kernels below.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_batch_f64(const ProblemDesc64 *__restrict__ probs, const int32_t *__restrict__ items,
-                 const int32_t *__restrict__ qb, int32_t nq, int32_t *__restrict__ counters) {
-    __shared__ int32_t sTile[64 * kTileStride];
-    __shared__ int32_t sBlk[128];
-    __shared__ int32_t sTerm[2 * kMaxClassTerms];
+                 const int32_t *__restrict__ qb, int32_t nq, int32_t *__restrict__ counters, int32_t max_terms,
+                 int32_t parts) {
+    extern __shared__ __align__(16) char smem[];
     __shared__ int32_t sItem;
+    const F64Lds lds = f64_lds(smem, max_terms);
     const int home = blockIdx.x % nq;
     int tried = 0;                       // queues found empty (thread 0)
     for (;;) {
-        if (threadIdx.x == 0) sItem = batch_next_item(qb, nq, counters, home, tried);
+        if (threadIdx.x == 0) sItem = batch_next_item(qb, nq, counters, home, tried, parts);
         __syncthreads();
         const int it = __builtin_amdgcn_readfirstlane(sItem);   // uniform: descriptors in scalar registers
         __syncthreads();                 // every thread has read sItem before it changes
         if (it < 0) break;
-        const ProblemDesc64 pd = probs[items[2 * it]];
-        const int item = items[2 * it + 1];
+        const int at = it / parts, part = it % parts;
+        const ProblemDesc64 pd = probs[items[2 * at]];
+        const int item = items[2 * at + 1];
         const int groups = pd.mtiles[4 * item + 2];
-        if (groups == 4) class_f64_tile<4, false>(pd, item, sTile, sBlk, sTerm);
-        else if (groups == 2) class_f64_tile<2, false>(pd, item, sTile, sBlk, sTerm);
-        else class_f64_tile<1, false>(pd, item, sTile, sBlk, sTerm);
+        if (groups == 4) class_f64_tile<4, false>(pd, item, part, parts, lds);
+        else if (groups == 2) class_f64_tile<2, false>(pd, item, part, parts, lds);
+        else class_f64_tile<1, false>(pd, item, part, parts, lds);
     }
 }
 
@@ -724,12 +962,12 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     // W[16 i + lr][8 lk + g] and M[8 lk + g][16 j + lr].
     auto step = [&](const Own &oc, int buf, const SAddr &sa, const OAddr &oa, int sbuf, Stage &stn, Own &on,
                     bool first, bool bar, int nse, int nsh, int noa, int noe, int noh, SAddr &sa_n, OAddr &oa_n,
-                    int stp, DCopy &dprev, auto symt, int ng, int g0, int g1) {
+                    int stp, DCopy<2> &dprev, auto symt, int ng, int g0, int g1) {
         constexpr bool S = decltype(symt)::value;
         stage_load(sa, stn);
         own_load(oa, on);
         if constexpr (WD) {
-            DCopy dc;
+            DCopy<2> dc;
             dcopy_load<NT>(pd.du64, pd.outD, sBlk, kDChunks, stp, wave, lane, dc);
             dcopy_store(dprev, lane);
             dprev = dc;
@@ -798,8 +1036,8 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     }
     SAddr sa = saddr(e1, 0);
     OAddr oa = oaddr(rw, 0, 1);
-    DCopy dpend;                           // D-hat chunks loaded, not yet stored
-    dpend.dst[0] = dpend.dst[1] = nullptr;
+    DCopy<2> dpend;                           // D-hat chunks loaded, not yet stored
+    dpend.clear();
     __syncthreads();
     // Symmetric classes (every term pairs a unique block with itself: the
     // blocks (J, J), with C[a][b] = C[b][a] bit for bit since the products
@@ -873,7 +1111,7 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     if constexpr (WD) {                  // the last step's chunks, then those past the last step
         dcopy_store(dpend, lane);
         for (int stp = 2 * RPW * nterms; 2 * NT * stp < kDChunks; ++stp) {
-            DCopy dc;
+            DCopy<2> dc;
             dcopy_load<NT>(pd.du64, pd.outD, sBlk, kDChunks, stp, wave, lane, dc);
             dcopy_store(dc, lane);
         }
@@ -1124,12 +1362,12 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     // operands written to buffer sbuf, and, at the end of a term, a barrier.
     auto step = [&](const Own &oc, int buf, const SAddr &sa, const OAddr &oa, int sbuf, Stage &stn, Own &on,
                     bool first, bool bar, int nse, int nsh, int noa, int noe, int noh, SAddr &sa_n, OAddr &oa_n,
-                    int stp, DCopy &dprev, auto symt, int ng, int g0, int g1) {
+                    int stp, DCopy<2> &dprev, auto symt, int ng, int g0, int g1) {
         constexpr bool S = decltype(symt)::value;
         stage_load(sa, stn);
         own_load(oa, on);
         if constexpr (WD) {
-            DCopy dc;
+            DCopy<2> dc;
             dcopy_load<NT>(pd.du64, pd.outD, sBlk, kDChunks, stp, wave, lane, dc);
             dcopy_store(dprev, lane);
             dprev = dc;
@@ -1219,8 +1457,8 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     }
     SAddr sa = saddr(e1, 0);
     OAddr oa = oaddr(rw, 0, 1);
-    DCopy dpend;                           // D-hat chunks loaded, not yet stored
-    dpend.dst[0] = dpend.dst[1] = nullptr;
+    DCopy<2> dpend;                           // D-hat chunks loaded, not yet stored
+    dpend.clear();
     __syncthreads();
     // Symmetric classes (every term pairs a unique block with itself: the
     // blocks (J, J), with C[a][b] = C[b][a] bit for bit since the products
@@ -1296,7 +1534,7 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     if constexpr (WD) {                  // the last step's chunks, then those past the last step
         dcopy_store(dpend, lane);
         for (int stp = 2 * RPW * nterms; 2 * NT * stp < kDChunks; ++stp) {
-            DCopy dc;
+            DCopy<2> dc;
             dcopy_load<NT>(pd.du64, pd.outD, sBlk, kDChunks, stp, wave, lane, dc);
             dcopy_store(dc, lane);
         }
@@ -1381,10 +1619,10 @@ hipError_t noalloc_scratch(int device, void **ptr) {
 }
 
 hipError_t launch_tabulate(const double *coef, int32_t lmax, double h, double *table,
-                           int32_t n_nodes, hipStream_t st) {
+                           int32_t n_nodes, int32_t *overflow, hipStream_t st) {
     const int threads = 256;
     const int blocks = (n_nodes + threads - 1) / threads;
-    hipLaunchKernelGGL(k_tabulate, dim3(blocks), dim3(threads), 0, st, coef, lmax, h, table, n_nodes);
+    hipLaunchKernelGGL(k_tabulate, dim3(blocks), dim3(threads), 0, st, coef, lmax, h, table, n_nodes, overflow);
     return hipGetLastError();
 }
 
@@ -1396,10 +1634,11 @@ hipError_t launch_eval(KTable kt, const double *y, double *out, int64_t n, hipSt
 }
 
 hipError_t launch_unique_eval(KTable kt, const UInfo *uinfo, int64_t nunique, const double *ring_theta,
-                              const double *ring_sin, double *u64, double *u64t, float *ut32, hipStream_t st) {
+                              const double *ring_sin, double *u64, double *u64t, float *ut32, const UnitMasks &um,
+                              hipStream_t st) {
     if (nunique == 0) return hipSuccess;
     hipLaunchKernelGGL(k_unique_eval, dim3((unsigned)nunique), dim3(256), 0, st, kt, uinfo, ring_theta,
-                       ring_sin, u64, u64t, ut32);
+                       ring_sin, u64, u64t, ut32, um);
     return hipGetLastError();
 }
 
@@ -1410,13 +1649,37 @@ hipError_t launch_expand(const double *u64, const int32_t *items, int64_t nitems
     return hipGetLastError();
 }
 
+// Dynamic LDS past 64 KiB is allowed per kernel: up to the largest class the
+// kernels hold, whatever this launch needs, so that launches do not lower each
+// other's limit.
+static hipError_t f64_allow_lds(const void *kernel, int bytes) {
+    if (bytes <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, f64_lds_bytes(kMaxClassTerms));
+}
+
+// A short launch splits each tile's row groups over up to eight workgroups, to
+// have two per CU (each repeats the tile's tables).  Measured, D-hat and
+// contraction, one / two / four / eight parts: 57 tiles (lmax 64) 518 / 322 /
+// 236 / 178 us, 208 (128) 460 / 308 / 265, 350 (256) 879 / 557 / 547, 987 (512)
+// 1270 / 1278 / 1321, 8848 (2048) 13373 / 13562 / 13916.
+static unsigned f64_parts(int64_t tiles) {
+    unsigned parts = 1;
+    while (parts < 8 && tiles * parts < 1024) parts *= 2;
+    return parts;
+}
+
 hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st) {
     if (a.nblocks == 0) return hipSuccess;
     if (prec == 0) {
         ProblemDesc64 pd{a.mtiles, a.classes, a.class_terms, a.class_blk, a.class_itab, a.u64t, a.ninv, a.out,
-                         a.du64, a.blk_uid, a.outD};
-        if (a.outD) hipLaunchKernelGGL(k_class_f64<true>, dim3((unsigned)a.nmtiles), dim3(256), 0, st, pd);
-        else hipLaunchKernelGGL(k_class_f64<false>, dim3((unsigned)a.nmtiles), dim3(256), 0, st, pd);
+                         a.du64, a.blk_uid, a.outD, a.masks.units, a.masks.cols, a.masks.overflow, a.max_terms};
+        const int lds = f64_lds_bytes(a.max_terms);
+        const void *k = a.outD ? (const void *)k_class_f64<true> : (const void *)k_class_f64<false>;
+        const hipError_t e = f64_allow_lds(k, lds);
+        if (e != hipSuccess) return e;
+        const dim3 grid((unsigned)a.nmtiles, f64_parts(a.nmtiles));
+        if (a.outD) hipLaunchKernelGGL(k_class_f64<true>, grid, dim3(256), lds, st, pd);
+        else hipLaunchKernelGGL(k_class_f64<false>, grid, dim3(256), lds, st, pd);
         return hipGetLastError();
     }
     if (prec == 1) {
@@ -1448,14 +1711,15 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t st) {
     if (b.prec == 0) {                   // FP64: N^-1 is read as given
         if (b.persistent) {
             if (b.nitems > 0)
-                hipLaunchKernelGGL(k_batch_f64, dim3((unsigned)b.nworkgroups), dim3(256), 0, st, b.desc64, b.items,
-                                   b.qb, b.nq, b.counters);
+                hipLaunchKernelGGL(k_batch_f64, dim3((unsigned)b.nworkgroups), dim3(256), f64_lds_bytes(b.max_terms), st,
+                                   b.desc64, b.items, b.qb, b.nq, b.counters, b.max_terms, (int32_t)f64_parts(b.nitems));
         } else {
             for (int p = 0; p < b.nprob; ++p) {
                 if (b.ngtiles[p] == 0) continue;
                 ProblemDesc64 d = b.host_desc64[p];
                 d.mtiles = b.gtiles[p];
-                hipLaunchKernelGGL(k_class_f64<false>, dim3((unsigned)b.ngtiles[p]), dim3(256), 0, st, d);
+                hipLaunchKernelGGL(k_class_f64<false>, dim3((unsigned)b.ngtiles[p], f64_parts(b.ngtiles[p])), dim3(256),
+                                   f64_lds_bytes(d.max_terms), st, d);
             }
         }
         return hipGetLastError();
@@ -1500,8 +1764,14 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t batch_occupancy(int prec, int *workgroups_per_cu) {
-    if (prec == 0) return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_f64, 256, 0);
+hipError_t batch_prepare(int prec, int max_terms, int *workgroups_per_cu) {
+    if (prec == 0) {
+        const int lds = f64_lds_bytes(max_terms);
+        hipError_t e = f64_allow_lds((const void *)k_batch_f64, lds);
+        if (e == hipSuccess) e = f64_allow_lds((const void *)k_class_f64<false>, lds);
+        if (e != hipSuccess) return e;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_f64, 256, lds);
+    }
     if (prec == 1) return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_f32, 512, 0);
     if (prec == 2) return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_bf16<2>, 512, 0);
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_bf16<3>, 512, 0);
