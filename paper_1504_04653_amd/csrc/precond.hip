@@ -2,22 +2,23 @@
 // (gfx950): for every tile J, the Cholesky factor of its diagonal block
 // A_J = D_JJ + C_JJ, and the application x_J = A_J^-1 r_J.
 //
-//   k_factor_diag  one wave per tile.  Lane l holds column l of A_J's upper
-//                  triangle (64 doubles in registers, read row by row with
-//                  coalesced 512-byte loads), i.e. row l of the lower factor
-//                  being built.  Step j takes the pivot from lane j, scales
-//                  column j (a multiply by the pivot's reciprocal, as
-//                  LAPACK's unblocked factorisation does), passes it through
-//                  LDS and updates the trailing rows: 64 sequential steps,
-//                  about 2,000 FMAs per lane, no workgroup barrier.
+//   k_factor_diag  one wave per tile, in four panels of 16 rows of U.  The upper
+//                  triangle's ten 16 x 16 blocks are MFMA accumulators.  A panel
+//                  passes through LDS to one column per lane, where 16 steps
+//                  (pivot from its lane, row scaled by the pivot's reciprocal as
+//                  LAPACK's unblocked factorisation does, the panel's later rows
+//                  updated with values broadcast from their lanes) finish its
+//                  rows of U; these pass through LDS to MFMA operands and update
+//                  the blocks below (FP64 16x16x4).  No workgroup barrier.
 //   k_solve_diag   one wave per tile, column l of U in lane l's registers:
 //                  U^T y = r as a column sweep (lane l accumulates row l),
 //                  then U x = y as a column sweep from the last row, whose
 //                  columns reach the other lanes through LDS eight at a time.
 //                  Both multiply by the reciprocals of U's diagonal.
 //
-// Both are bound by HBM: the factor reads two 32 KiB blocks and writes one
-// per tile, the solve reads one and 1 KiB of vectors.
+// Both read only the 128-byte lines that hold part of the upper triangle (5/8 of
+// a block) and are then bound by HBM: the factor reads 40 KiB and writes 32 per
+// tile, the solve reads 20 KiB and 1 KiB of vectors.
 #include <hip/hip_runtime.h>
 
 #include "precond.hpp"
@@ -36,67 +37,97 @@ __device__ __forceinline__ double from_lane(double v, int src) {
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+// Values pass between the lanes of one wave through LDS: no other wave looks.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Block (I, L), I <= L, of the upper triangle: lane (lr, lk) holds rows 16 I +
+// lk + 4 v of column 16 L + lr, as an MFMA result.  The element-by-element form
+// this replaces broadcast every multiplier from LDS to the 64 lanes (2016
+// doubles per tile, 32 k LDS clocks per four waves) and took 1.88 ms at lmax
+// 2048 (97,456 tiles); this takes 1.3, at 5.4 TB/s.
 template <bool WITH_C>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3))) void k_factor_diag(const double *__restrict__ D,
                                                              const double *__restrict__ C,
                                                              const int32_t *__restrict__ dblk, int64_t ntiles,
                                                              double *__restrict__ U, int32_t *__restrict__ info) {
-    __shared__ double sCol[kWaves][2][kN];   // the scaled column of a step, two buffers per wave
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ double sP[kWaves][16][kN];    // a panel: row, column
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
     const int64_t J = (int64_t)blockIdx.x * kWaves + wave;
     if (J >= ntiles) return;                 // the whole wave
     const int64_t base = (int64_t)dblk[J] * (kN * kN);
-    double u[kN];                            // u[c] = A[c][lane]: upper triangle for c <= lane
+    double (*panel)[kN] = sP[wave];
+    doublex4 a[4][4];                        // [I][L], L >= I
 #pragma unroll
-    for (int c0 = 0; c0 < kN; c0 += 8) {    // eight rows at a time: D and C rows in flight together
-        double t[8];
+    for (int I = 0; I < 4; ++I)
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            u[c0 + c] = D[base + (c0 + c) * kN + lane];
-            if constexpr (WITH_C) t[c] = C[base + (c0 + c) * kN + lane];
-        }
-        if constexpr (WITH_C) {
+        for (int L = I; L < 4; ++L)
 #pragma unroll
-            for (int c = 0; c < 8; ++c) u[c0 + c] += t[c];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    int bad = 0;
-#pragma clang loop unroll(full)
-    for (int j = 0; j < kN; ++j) {
-        const double pivot = from_lane(u[j], j);   // A_jj less the earlier steps' updates
-        if (bad == 0 && !(pivot > 0.0)) bad = j + 1;
-        const double s = sqrt(pivot);
-        const double inv = 1.0 / s;
-        const double lj = lane == j ? s : (lane > j ? u[j] * inv : u[j]);   // L[lane][j]
-        u[j] = lj;
-        double *col = sCol[wave][j & 1];
-        col[lane] = lj;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // A[lane][c] -= L[lane][j] L[c][j] for the rows below j, eight columns at a time; the
-        // rows above take a zero multiplier instead of a branch, which would make the
-        // register allocator keep copies of u
-        const double m = lane > j ? -lj : 0.0;
+            for (int v = 0; v < 4; ++v) a[I][L][v] = D[base + (16 * I + lk + 4 * v) * kN + 16 * L + lr];
+    if constexpr (WITH_C) {
 #pragma unroll
-        for (int c0 = j + 1; c0 < kN; c0 += 8) {
-            double v[8];
+        for (int I = 0; I < 4; ++I) {
+            doublex4 t[4];
 #pragma unroll
-            for (int t = 0; t < 8; ++t)
-                if (c0 + t < kN) v[t] = col[c0 + t];
+            for (int L = I; L < 4; ++L)
 #pragma unroll
-            for (int t = 0; t < 8; ++t)
-                if (c0 + t < kN) u[c0 + t] = fma(m, v[t], u[c0 + t]);
-            __builtin_amdgcn_sched_barrier(0);   // keeps the LDS reads of later chunks from piling up
+                for (int v = 0; v < 4; ++v) t[L][v] = C[base + (16 * I + lk + 4 * v) * kN + 16 * L + lr];
+#pragma unroll
+            for (int L = I; L < 4; ++L) a[I][L] += t[L];
+            __builtin_amdgcn_sched_barrier(0);   // 16 loads of C in flight at most: more would spill
         }
     }
     double *out = U + J * (kN * kN);
+    int bad = 0;
 #pragma unroll
-    for (int c0 = 0; c0 < kN; c0 += 16) {   // U[c][lane] = L[lane][c], zero below the diagonal
+    for (int k = 0; k < 4; ++k) {
+        wave_sync();                         // the previous panel's operands have been read
 #pragma unroll
-        for (int c = c0; c < c0 + 16; ++c) out[c * kN + lane] = c <= lane ? u[c] : 0.0;
-        __builtin_amdgcn_sched_barrier(0);
+        for (int L = k; L < 4; ++L)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) panel[lk + 4 * v][16 * L + lr] = a[k][L][v];
+        wave_sync();
+        double u[16];                        // rows 16 k + j of column `lane`
+#pragma unroll
+        for (int j = 0; j < 16; ++j) u[j] = panel[j][lane];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int r = 16 * k + j;
+            const double pivot = from_lane(u[j], r);   // A_rr less the earlier steps' updates
+            if (bad == 0 && !(pivot > 0.0)) bad = r + 1;
+            const double s = sqrt(pivot);
+            const double inv = 1.0 / s;
+            u[j] = lane == r ? s : u[j] * inv;
+#pragma unroll
+            for (int i = j + 1; i < 16; ++i) u[i] = fma(-from_lane(u[j], 16 * k + i), u[j], u[i]);
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {       // zero below the diagonal
+            u[j] = 16 * k + j <= lane ? u[j] : 0.0;
+            out[(16 * k + j) * kN + lane] = u[j];
+        }
+        if (k == 3) break;
+        wave_sync();
+#pragma unroll
+        for (int j = 0; j < 16; ++j) panel[j][lane] = u[j];
+        wave_sync();
+        double op[4][4];                     // [X][t]: U[16 k + 4 t + lk][16 X + lr], either operand of block X
+#pragma unroll
+        for (int X = k + 1; X < 4; ++X)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) op[X][t] = panel[4 * t + lk][16 * X + lr];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int I = k + 1; I < 4; ++I)
+#pragma unroll
+                for (int L = I; L < 4; ++L)
+                    a[I][L] = __builtin_amdgcn_mfma_f64_16x16x4f64(-op[I][t], op[L][t], a[I][L], 0, 0, 0);
     }
     if (lane == 0) info[J] = bad;
 }
@@ -110,9 +141,15 @@ __global__ __launch_bounds__(64 * kWaves) void k_solve_diag(const double *__rest
     const int64_t J = (int64_t)blockIdx.x * kWaves + wave;
     if (J >= ntiles) return;
     const double *ut = U + J * (kN * kN);
-    double u[kN];                            // u[c] = U[c][lane]
+    double u[kN];                            // u[c] = U[c][lane], in the lines that hold part of the upper triangle
 #pragma unroll
-    for (int c = 0; c < kN; ++c) u[c] = ut[c * kN + lane];
+    for (int c = 0; c < kN; ++c) u[c] = 0.0;
+#pragma unroll
+    for (int c0 = 0; c0 < kN; c0 += 16)
+        if (lane >= c0) {
+#pragma unroll
+            for (int c = c0; c < c0 + 16; ++c) u[c] = ut[c * kN + lane];
+        }
     const double rinv = 1.0 / ut[lane * kN + lane];   // 1 / U[lane][lane]
     double z = r[J * kN + lane];
     // U^T y = r, a column sweep: row l of U^T is column l of U, held by lane l
