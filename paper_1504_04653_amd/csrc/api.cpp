@@ -163,6 +163,7 @@ struct sympix_kernel {
     float *ut32 = nullptr;
     double *u64t = nullptr;
     sympix::UnitMasks masks = {};
+    bool short_cut = false;
     void *block = nullptr;    // one stream-ordered allocation holding all of the above
 };
 
@@ -446,6 +447,7 @@ sympix_status sample_btnb(const sympix_grid *g, const sympix_kernel *d, const sy
     a.u64t = b->u64t;
     a.ut32 = b->ut32;
     a.masks = b->masks;
+    a.skip = b->short_cut ? 1 : 0;
     if (pat) {
         const DevClasses *dc = nullptr;
         s = two_hop_tables(g, b->device, &pat, &dc);
@@ -483,6 +485,7 @@ struct TabSource {
     int64_t nunique;
     const UInfo *uinfo;
     const double *ring_theta, *ring_sin;
+    int64_t npix;             // of the grid of the unknowns
 };
 
 sympix_status tabulate(const TabSource &src, const sympix_grid *g, const sympix_cross *x, int device,
@@ -507,6 +510,7 @@ sympix_status tabulate(const TabSource &src, const sympix_grid *g, const sympix_
         kr->y_cut = 2.0 * sr * sr;
         if (kr->y_cut < y_dom) y_dom = kr->y_cut;
     }
+    kr->short_cut = sympix::short_cut(radius, std::sqrt(4.0 * kPi / (double)src.npix));
     // nodes uniform in s = sqrt(y) up to the domain end plus a little slack for
     // device rounding of y; the last interval keeps one spare node
     const double s_top = std::fmax(std::sqrt(y_dom) * (1.0 + 1e-6), 1e-300);
@@ -714,7 +718,7 @@ sympix_status sympix_kernel_tabulate(const sympix_grid *g, const double *coef_l,
     sympix_status s = device_tables(g, device, &dg);
     if (s != SYMPIX_OK) return s;
     const Geometry &geo = g->geo;
-    TabSource src{geo.lmax, geo.y_pattern_max, geo.nunique(), dg->uinfo, dg->ring_theta, dg->ring_sin};
+    TabSource src{geo.lmax, geo.y_pattern_max, geo.nunique(), dg->uinfo, dg->ring_theta, dg->ring_sin, geo.npix};
     return tabulate(src, g, nullptr, device, coef_l, ncoef, radius, n_nodes, (hipStream_t)stream, out);
 }
 
@@ -1132,10 +1136,14 @@ sympix_status sympix_batch_create(const sympix_problem *p, int32_t n, int32_t pr
                                       p[i].b->masks.units, p[i].b->masks.cols, p[i].b->masks.overflow, bt->max_terms};
             bt->hdesc64[t].push_back(d64);
             sympix::ProblemDesc d{dtiles, dg->classes, dg->class_terms, dg->class_blk, dg->class_itab,
-                                  p[i].b->ut32, nullptr, p[i].out_dev, nullptr, nullptr, nullptr};
+                                  p[i].b->ut32, nullptr, p[i].out_dev, nullptr, nullptr, nullptr,
+                                  p[i].b->masks.units, p[i].b->masks.cols, p[i].b->masks.overflow,
+                                  p[i].b->short_cut ? 1 : 0};
             bt->hdesc[t].push_back(d);
             sympix::ProblemDescB db{dtiles, dg->classes, dg->class_terms, dg->class_blk, dg->class_itab,
-                                    p[i].b->ut32, {nullptr, nullptr, nullptr}, p[i].out_dev, nullptr, nullptr, nullptr};
+                                    p[i].b->ut32, {nullptr, nullptr, nullptr}, p[i].out_dev, nullptr, nullptr, nullptr,
+                                    p[i].b->masks.units, p[i].b->masks.cols, p[i].b->masks.overflow,
+                                    p[i].b->short_cut ? 1 : 0};
             bt->hdescb[t].push_back(db);
             const int64_t nmt = (int64_t)tiles.size() / 4;
             const std::vector<int32_t> &gt = t == SYMPIX_TILES_64 ? geo.cls.gtiles : geo.cls.gtiles32;
@@ -1499,7 +1507,8 @@ sympix_status sympix_kernel_tabulate_cross(const sympix_cross *c, const double *
     const DevCross *dx = nullptr;
     sympix_status s = cross_tables(c, device, &dx);
     if (s != SYMPIX_OK) return s;
-    TabSource src{c->x.lmax_eff, c->x.y_pattern_max, c->x.nunique(), dx->uinfo, dx->ring_theta, dx->ring_sin};
+    TabSource src{c->x.lmax_eff, c->x.y_pattern_max, c->x.nunique(), dx->uinfo, dx->ring_theta, dx->ring_sin,
+                  c->g1->geo.npix};
     return tabulate(src, nullptr, c, device, coef_l, ncoef, radius, n_nodes, (hipStream_t)stream, out);
 }
 
@@ -1549,6 +1558,7 @@ sympix_status sympix_sample_BtNB_cross(const sympix_cross *c, const sympix_kerne
     a.u64t = b->u64t;
     a.ut32 = b->ut32;
     a.masks = b->masks;
+    a.skip = b->short_cut ? 1 : 0;
     a.classes = dx->classes;
     a.class_terms = dx->class_terms;
     a.class_blk = dx->class_blk;

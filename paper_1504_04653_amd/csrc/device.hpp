@@ -38,7 +38,7 @@ struct KTable {
 // column q the units, four columns of a ring of tile I, that are not all zero
 // (bit 8 h + r: ring r, columns 4 h .. 4 h + 3, i.e. rows p = 32 h + 8 l + r,
 // l = 0 .. 3), the same of each group of 16 columns, and whether any element
-// of any block is not finite (a table that overflowed).
+// of any block is not finite in FP32 (a table that overflowed).
 struct UnitMasks {
     uint16_t *units;      // [nunique][64]
     uint16_t *cols;       // [nunique][4]
@@ -86,12 +86,19 @@ struct BtnbArgs {
     double *out;
     UnitMasks masks;          // of the unique blocks u64t / ut32
     int32_t max_terms;        // most terms of a class
+    int32_t skip;             // the kernel's cut is short_cut
     // optional D-hat blocks written by the same launch:
     // stored block n gets unique block blk_uid[n] of du64 (row-major FP64)
     const double *du64;
     const int32_t *blk_uid;
     double *outD;             // nullptr: B-hat^T N^-1 B-hat only
 };
+// Whether a radial cut is short enough for the FP32 and split-BF16 forms to test
+// their MFMAs against the masks.  Measured, lmax 1500, every MFMA / tests: FP32
+// cut at 9 mean pixel spacings 7.00 / 5.55 ms, at 15 6.99 / 7.37 (the two lines
+// cross near 13.5); BF16x6 4.92 / 4.40 and 5.15 / 5.21.  (The FP64 form tests at
+// every cut: 23.6 -> 21.8 ms at 15 spacings, lmax 2048.)
+inline bool short_cut(double radius, double spacing) { return radius > 0 && radius < 12.5 * spacing; }
 hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st);
 
 // Operands of the FP64 class GEMM (device pointers).
@@ -121,6 +128,9 @@ struct ProblemDescB {
     const double *du64;       // D-hat: unique blocks, row-major FP64 (with outD)
     const int32_t *blk_uid;   // unique block of each stored block
     double *outD;             // D-hat output, or nullptr
+    const uint16_t *units, *unit_cols;   // UnitMasks of ut32
+    const int32_t *overflow;
+    int32_t skip;             // leave out products that the masks make zero (short_cut)
 };
 
 // Operands of the FP32 class GEMM for one problem (device pointers).
@@ -134,6 +144,9 @@ struct ProblemDesc {
     const double *du64;       // D-hat: unique blocks, row-major FP64 (with outD)
     const int32_t *blk_uid;   // unique block of each stored block
     double *outD;             // D-hat output, or nullptr
+    const uint16_t *units, *unit_cols;   // UnitMasks of ut32
+    const int32_t *overflow;
+    int32_t skip;             // leave out products that the masks make zero (short_cut)
 };
 
 // a10: one batched launch.  host_desc / host_descb / host_desc64 / ninv /

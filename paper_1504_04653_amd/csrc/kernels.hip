@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256) void k_unique_eval(KTable kt, const UInfo *__r
         lo |= lo >> 16;
         hi |= hi >> 16;
         const uint32_t nz = ((lo | lo >> 8) & 255u) | ((hi | hi >> 8) & 255u) << 8;
-        const bool over = __any(!(fabs(v) < INFINITY));
+        const bool over = __any(!(fabsf((float)v) < INFINITY));
         if (p == 0) {
             um.units[uid * 64 + q] = (uint16_t)nz;
             atomicOr(&scols[q >> 4], nz);
@@ -431,7 +431,6 @@ struct F64Lds {
     char *stage;
     int32_t *blk;               // [192]: stored block per member row; its D-hat source block; and the stored
                                 // blocks again, at 16 i + 4 lk + v that of row 16 i + lk + 4 v
-    int32_t *bad;               // N^-1 of the tile holds a value that is not finite
     uint16_t *mask;             // [64 * S]: units of (term, row a) in which B_IJ is not all zero
     uint16_t *cols;             // [4 * S]: units of (term, column group j) in which B_IK is not all zero
     uint32_t *on;               // [4][3][4 * S]: per wave, steps of three row groups: bit 4 q + t for MFMA t of accumulator q
@@ -442,15 +441,14 @@ struct F64Lds {
 };
 
 __host__ __device__ constexpr int f64_lds_bytes(int S) {
-    return 3 * kStage + 4 * (192 + 8) + 2 * (64 + 4 + 48) * S + 4 * (48 * S + 2 * S + 64 * (S | 1));
+    return 3 * kStage + 4 * 192 + 2 * (64 + 4 + 48) * S + 4 * (48 * S + 2 * S + 64 * (S | 1));
 }
 
 __device__ __forceinline__ F64Lds f64_lds(char *p, int S) {
     F64Lds l;
     l.stage = p;
     l.blk = (int32_t *)(p + 3 * kStage);
-    l.bad = l.blk + 192;
-    l.mask = (uint16_t *)(l.bad + 8);          // 8-byte aligned, as cols: read four at a time
+    l.mask = (uint16_t *)(l.blk + 192);          // 8-byte aligned, as cols: read four at a time
     l.cols = l.mask + 64 * S;
     l.code = l.cols + 4 * S;
     l.term = (int32_t *)(l.code + 48 * S);
@@ -520,18 +518,20 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
         ((uint32_t *)lds.mask)[x] = ((const uint32_t *)pd.units)[(int64_t)terms[2 * (x >> 5)] * 32 + (x & 31)];
     for (int x = tid; x < 4 * nterms; x += 256)
         lds.cols[x] = pd.unit_cols[(int64_t)terms[2 * (x >> 2) + 1] * 4 + (x & 3)];
-    if (tid == 0) *lds.bad = *pd.overflow;
     __syncthreads();
-    bool bad = false;                    // sixteen threads per (member row, term), four pixels each
+    bool bad = *pd.overflow != 0;        // sixteen threads per (member row, term), four pixels each
     for (int r = tid >> 4; r < 16 * NI; r += 16)
-        for (int e = 0; e < nterms; ++e) {
-            const doublex4 v = *(const doublex4 *)(wv + (int64_t)lds.tile[r * lds.stride + e] * 64 + 4 * lr);
+        for (int e = 0; e < nterms; e += 4) {        // four loads in flight
+            doublex4 v[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) bad |= not_finite(v[t]);
+            for (int i = 0; i < 4; ++i)
+                v[i] = *(const doublex4 *)(wv + (int64_t)lds.tile[r * lds.stride + min(e + i, nterms - 1)] * 64 + 4 * lr);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) bad |= not_finite(v[i][t]);
         }
-    if (bad) *lds.bad = 1;
-    __syncthreads();
-    if (*lds.bad != 0) {
+    if (__syncthreads_or(bad)) {
         for (int x = tid; x < 32 * nterms; x += 256) ((uint32_t *)lds.mask)[x] = 0xffffffffu;
         for (int x = tid; x < 2 * nterms; x += 256) ((uint32_t *)lds.cols)[x] = 0xffffffffu;
         __syncthreads();
@@ -871,6 +871,75 @@ void k_batch_f64(const ProblemDesc64 *__restrict__ probs, const int32_t *__restr
 // pixels is added to FP64 accumulators, which are stored and cleared at the
 // end of every row a.
 // ---------------------------------------------------------------------------
+// What a member tile of the FP32 and split-BF16 kernels leaves out, in LDS: the
+// masks of its class's terms (as in the FP64 form) and, row quad by row quad (a
+// = 4 x .. 4 x + 3, one row per row phase), the terms in which any of the four
+// rows and any column can be nonzero, 256 x + term, at least one per quad.  A
+// term's steps and its sum stay together, so the results are those of the
+// full contraction bit for bit.  An FP32 wave tests each MFMA (a unit of one
+// column group), a split-BF16 one each half term (its products are split and
+// scheduled together).  Measured, beam 3 pixels, lmax 1500, contraction: FP32
+// 7.00 -> 5.55 ms, BF16x6 4.92 -> 4.40; FP32 on the two-hop pattern (lmax 701,
+// 2.3 pixels) 3.06 -> 1.77.
+struct SkipLds {
+    uint16_t mask[kMaxClassTerms * 64];   // units of (term, row a) in which B_IJ is not all zero
+    uint16_t cols[kMaxClassTerms * 4];    // units of (term, column group j) in which B_IK is not all zero
+    uint16_t list[16 * kMaxClassTerms];
+};
+
+// Fills it (512 threads; sTerm and the tile's W are there): w_finite(r, e, c)
+// tells whether pixels 4 c .. 4 c + 3 of member row r, term e are finite.  Only
+// the row quads of this part of the tile are listed.  Returns the length of the
+// list.
+template <int NI, class PD, class Finite>
+__device__ __forceinline__ int build_skip(const PD &pd, int nterms, int part, int parts, const int32_t *sTerm, SkipLds &sk,
+                                          const Finite &w_finite) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int x = tid; x < 32 * nterms; x += 512)
+        ((uint32_t *)sk.mask)[x] = ((const uint32_t *)pd.units)[(int64_t)sTerm[2 * (x >> 5)] * 32 + (x & 31)];
+    for (int x = tid; x < 4 * nterms; x += 512) sk.cols[x] = pd.unit_cols[(int64_t)sTerm[2 * (x >> 2) + 1] * 4 + (x & 3)];
+    bool bad = *pd.overflow != 0;        // sixteen threads per (member row, term), four pixels each
+    for (int r = tid >> 4; r < 16 * NI; r += 32)
+        for (int e = 0; e < nterms; e += 8) {        // eight loads in flight
+            bool b[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) b[i] = !w_finite(r, min(e + i, nterms - 1), tid & 15);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) bad |= b[i];
+        }
+    if (__syncthreads_or(bad)) {
+        for (int x = tid; x < 32 * nterms; x += 512) ((uint32_t *)sk.mask)[x] = 0xffffffffu;
+        for (int x = tid; x < 2 * nterms; x += 512) ((uint32_t *)sk.cols)[x] = 0xffffffffu;
+        __syncthreads();
+    }
+    // every wave writes the same list, and reads what it wrote itself
+    int total = 0;
+    for (int x = 16 * part / parts; x < 16 * (part + 1) / parts; ++x) {
+        const int first = total;
+        for (int e0 = 0; e0 < nterms; e0 += 64) {
+            const int e = min(e0 + lane, nterms - 1);
+            const uint64_t m = *(const uint64_t *)(sk.mask + 64 * e + 4 * x), c = *(const uint64_t *)(sk.cols + 4 * e);
+            uint32_t mm = (uint32_t)m | (uint32_t)(m >> 32), cc = (uint32_t)c | (uint32_t)(c >> 32);
+            mm |= mm >> 16;
+            cc |= cc >> 16;
+            const bool take = e0 + lane < nterms && (mm & cc & 0xffffu) != 0;
+            const uint64_t b = __ballot(take);
+            if (take)
+                sk.list[total + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0))] =
+                    (uint16_t)(256 * x + e);
+            total += __popcll(b);
+        }
+        if (total == first) {
+            if (lane == 0) sk.list[total] = (uint16_t)(256 * x);
+            ++total;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    return __builtin_amdgcn_readfirstlane(total);
+}
+
 __global__ __launch_bounds__(256) void k_ninv_f32(const double *__restrict__ ninv, int64_t n,
                                                   float *__restrict__ wf) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -880,9 +949,9 @@ __global__ __launch_bounds__(256) void k_ninv_f32(const double *__restrict__ nin
 // One member tile (item) of one problem with NI groups of 16 member rows; all
 // 512 threads of the workgroup take part.  sTile / sBlk / sTerm are the
 // workgroup's LDS tables, sW / sU its four staging buffers.
-template <int NI, bool WD>
-__device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, int32_t *sTile,
-                                               int32_t *sBlk, int32_t *sTerm, floatx4 *sW, floatx4 *sU) {
+template <int NI, bool WD, bool SKIP>
+__device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, int part, int parts, int32_t *sTile,
+                                               int32_t *sBlk, int32_t *sTerm, floatx4 *sW, floatx4 *sU, SkipLds &sk) {
     const float *__restrict__ ut32 = pd.ut32;
     double *__restrict__ out = pd.out;
     constexpr int NW = 8, NT = 64 * NW, RP = NW / 2, RPW = 64 / RP;
@@ -895,7 +964,7 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     const int nterms = cl.nterms;
     const int32_t *terms = pd.cterms + 2 * cl.term0;
     if (nterms == 0) {
-        empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI);
+        if (part == 0) empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI);
         return;
     }
 
@@ -911,6 +980,13 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     }
     if (tid < 2 * nterms) sTerm[tid] = terms[tid];   // unique-block pairs of the class
     __syncthreads();
+    // SKIP false: every term of every row, in order
+    const int quad0 = 16 * part / parts;
+    int total = (16 * (part + 1) / parts - quad0) * nterms;
+    if constexpr (SKIP) total = build_skip<NI>(pd, nterms, part, parts, sTerm, sk, [&](int r, int e, int c) {
+        const floatx4 v = *(const floatx4 *)(pd.wf + (int64_t)sTile[r * kTileStride + e] * 64 + 4 * c);
+        return fabsf(v[0]) < INFINITY && fabsf(v[1]) < INFINITY && fabsf(v[2]) < INFINITY && fabsf(v[3]) < INFINITY;
+    });
 
     // Staging of one step (32 pixels of a term): W of the tile's 64 rows and
     // the B_IK values of its 64 columns, FP32, 8 chunks of 16 bytes per row
@@ -949,10 +1025,12 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
         sW[buf * 512 + sdst] = st.w;
         sU[buf * 512 + sdst] = st.u;
     };
-    constexpr int kDChunks = 16 * NI * 2048;   // D-hat chunks of the tile
+    // this part's D-hat chunks of the tile, two per thread and step: steps dstep .. dchunks / (2 NT)
+    constexpr int kDSteps = 16 * NI * 2048 / (2 * NT);
+    const int dstep = kDSteps * part / parts, dchunks = kDSteps * (part + 1) / parts * 2 * NT;
 
     doublex4 acc[NI][2];
-    floatx4 part[NI][2];
+    floatx4 psum[NI][2];
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -961,14 +1039,14 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     // g (g = 0..7) of a step takes the pixels 8 lk + g: lane (lr, lk) holds
     // W[16 i + lr][8 lk + g] and M[8 lk + g][16 j + lr].
     auto step = [&](const Own &oc, int buf, const SAddr &sa, const OAddr &oa, int sbuf, Stage &stn, Own &on,
-                    bool first, bool bar, int nse, int nsh, int noa, int noe, int noh, SAddr &sa_n, OAddr &oa_n,
+                    int h, uint32_t on0, uint32_t on1, bool bar, int nse, int nsh, int noa, int noe, int noh, SAddr &sa_n, OAddr &oa_n,
                     int stp, DCopy<2> &dprev, auto symt, int ng, int g0, int g1) {
         constexpr bool S = decltype(symt)::value;
         stage_load(sa, stn);
         own_load(oa, on);
         if constexpr (WD) {
             DCopy<2> dc;
-            dcopy_load<NT>(pd.du64, pd.outD, sBlk, kDChunks, stp, wave, lane, dc);
+            dcopy_load<NT>(pd.du64, pd.outD, sBlk, dchunks, stp, wave, lane, dc);
             dcopy_store(dprev, lane);
             dprev = dc;
         }
@@ -982,7 +1060,9 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
         }
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj) {
-            if (S && jj >= ng) continue;     // symmetric class: this wave's groups of the row
+            // bit g: ring g of this half's four columns can be nonzero
+            const uint32_t rings = (jj ? on1 : on0) >> (8 * h) & 255u;
+            if ((SKIP || S) && rings == 0) continue;
             const int b = S ? 16 * (jj ? g1 : g0) + lr : 32 * ch + 16 * jj + lr;
             float m[8];
 #pragma unroll
@@ -993,10 +1073,12 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
             }
 #pragma unroll
             for (int g = 0; g < 8; ++g)
+                if (!SKIP || (rings & (1u << g)) != 0) {
 #pragma unroll
-                for (int i = 0; i < NI; ++i)
-                    part[i][jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                        wfr[i][g >> 2][g & 3], m[g], (first && g == 0) ? floatx4{0.f, 0.f, 0.f, 0.f} : part[i][jj], 0, 0, 0);
+                    for (int i = 0; i < NI; ++i)
+                        psum[i][jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(wfr[i][g >> 2][g & 3], m[g],
+                                                                           !SKIP && h == 0 && g == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : psum[i][jj], 0, 0, 0);
+                }
         }
         sa_n = saddr(nse, nsh);
         oa_n = oaddr(noa, noe, noh);
@@ -1009,33 +1091,49 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     // Four LDS buffers: iteration it (one term of one row) computes from
     // buffers 2 (it & 1) + h, fills the other pair for iteration it + 1, and
     // ends with the only barrier of the term.
-    auto next = [&](int cx, int ce, int &nx, int &ne) {
-        ne = ce + 1;
-        nx = cx;
-        if (ne == nterms) {
-            ne = 0;
-            ++nx;
+    // entry it of the list (past its end the last one), and this wave's MFMAs of
+    // an entry, read one iteration ahead: bit 8 h + g of a column group
+    auto entry = [&](int it, int before) {   // before: entry it - 1
+        if constexpr (SKIP) return (int)sk.list[min(it, total - 1)];
+        else if (it == 0) return 256 * quad0;
+        else if (it >= total) return before;
+        else return (before & 255) + 1 < nterms ? before + 1 : (before | 255) + 1;
+    };
+    auto uniform = [&](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    struct Groups { int ng, g0, g1; };
+    auto groups_of = [&](auto symt, int x) {
+        Groups q{2, 2 * ch, 2 * ch + 1};
+        if constexpr (decltype(symt)::value) {
+            const int p = x >> 2;
+            if (p == 1 && ch == 0) q = Groups{1, 1, 1};
+            else if (p == 2) q = Groups{1, 2 + ch, 2 + ch};
+            else if (p == 3) q = Groups{ch, 3, 3};
         }
-        if (nx >= RPW) {
-            nx = cx;
-            ne = ce;
+        return q;
+    };
+    auto on_of = [&](int c, const Groups &q, uint32_t &o0, uint32_t &o1) {
+        if constexpr (!SKIP) {
+            o0 = q.ng > 0 ? 0xffffu : 0u;
+            o1 = q.ng > 1 ? 0xffffu : 0u;
+        } else {
+            const uint32_t m = sk.mask[64 * (c & 255) + rw + RP * (c >> 8)];
+            o0 = q.ng > 0 ? m & sk.cols[4 * (c & 255) + q.g0] : 0u;
+            o1 = q.ng > 1 ? m & sk.cols[4 * (c & 255) + q.g1] : 0u;
         }
     };
     Stage s0, s1;
     Own o0, o1;
-    int x = 0, e = 0;
-    int x1, e1;
-    next(0, 0, x1, e1);
+    int c0 = uniform(entry(0, 0)), c1 = uniform(entry(1, c0));   // this iteration and the next
     {
         Stage t0, t1;
-        stage_load(saddr(0, 0), t0);
-        stage_load(saddr(0, 1), t1);
-        own_load(oaddr(rw, 0, 0), o0);
+        stage_load(saddr(c0 & 255, 0), t0);
+        stage_load(saddr(c0 & 255, 1), t1);
+        own_load(oaddr(rw + RP * (c0 >> 8), c0 & 255, 0), o0);
         stage_store(t0, 0);
         stage_store(t1, 1);
     }
-    SAddr sa = saddr(e1, 0);
-    OAddr oa = oaddr(rw, 0, 1);
+    SAddr sa = saddr(c1 & 255, 0);
+    OAddr oa = oaddr(rw + RP * (c0 >> 8), c0 & 255, 1);
     DCopy<2> dpend;                           // D-hat chunks loaded, not yet stored
     dpend.clear();
     __syncthreads();
@@ -1049,38 +1147,39 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     // x / 4 = 0: {0, 1} | {2, 3};  1: {1} | {2, 3};  2: {2} | {3};  3: {} | {3}.
     auto rows = [&](auto symt) {
         constexpr bool S = decltype(symt)::value;
-        for (int it = 0; it < RPW * nterms; ++it) {
-            next(x, e, x1, e1);
+        Groups gr = groups_of(symt, c0 >> 8);
+        uint32_t on0, on1;
+        on_of(c0, gr, on0, on1);
+        on0 = uniform(on0);
+        on1 = uniform(on1);
+        for (int it = 0; it < total; ++it) {
+            const int raw2 = entry(it + 2, c1);
+            const int x = c0 >> 8, x1 = c1 >> 8, e1 = c1 & 255, p = x >> 2;
             const int a = rw + RP * x, a1 = rw + RP * x1;
-            int x2, e2;
-            next(x1, e1, x2, e2);
-            const int p = x >> 2;
-            int ng = 2, g0 = 2 * ch, g1 = 2 * ch + 1;
-            if constexpr (S) {
-                if (p == 1 && ch == 0) {
-                    ng = 1;
-                    g0 = 1;
-                } else if (p == 2) {
-                    ng = 1;
-                    g0 = 2 + ch;
-                } else if (p == 3) {
-                    ng = ch;
-                    g0 = 3;
-                }
+            const int ng = gr.ng, g0 = gr.g0, g1 = gr.g1;
+            const Groups gn = groups_of(symt, x1);
+            uint32_t raw_on0, raw_on1;
+            on_of(c1, gn, raw_on0, raw_on1);
+            if constexpr (SKIP) {
+#pragma unroll
+                for (int i = 0; i < NI; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) psum[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
             const int ib = 2 * (it & 1), nb = 2 - ib;
-            step(o0, ib, sa, oa, nb, s1, o1, true, false, e1, 1, a1, e1, 0, sa, oa, 2 * it, dpend, symt, ng, g0, g1);
-            step(o1, ib + 1, sa, oa, nb + 1, s0, o0, false, true, e2, 0, a1, e1, 1, sa, oa, 2 * it + 1, dpend, symt,
+            step(o0, ib, sa, oa, nb, s1, o1, 0, on0, on1, false, e1, 1, a1, e1, 0, sa, oa, dstep + 2 * it, dpend, symt, ng, g0, g1);
+            const int c2 = uniform(raw2);
+            step(o1, ib + 1, sa, oa, nb + 1, s0, o0, 1, on0, on1, true, c2 & 255, 0, a1, e1, 1, sa, oa, dstep + 2 * it + 1, dpend, symt,
                  ng, g0, g1);
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
-                    if (!S || j < ng) {
+                    if ((!SKIP && !S) || (j ? on1 : on0) != 0) {
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[i][j][v] += (double)part[i][j][v];
+                        for (int v = 0; v < 4; ++v) acc[i][j][v] += (double)psum[i][j][v];
                     }
-            if (e == nterms - 1) {           // end of output row a: store, clear
+            if (x1 != x || it + 1 == total) {    // end of output row a: store, clear
 #pragma unroll
                 for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -1102,30 +1201,38 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
 #pragma unroll
                     for (int j = 0; j < 2; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
             }
-            x = x1;
-            e = e1;
+            c0 = c1;
+            c1 = c2;
+            on0 = uniform(raw_on0);
+            on1 = uniform(raw_on1);
+            gr = gn;
         }
     };
     if (cl.sym != 0) rows(std::true_type());
     else rows(std::false_type());
     if constexpr (WD) {                  // the last step's chunks, then those past the last step
         dcopy_store(dpend, lane);
-        for (int stp = 2 * RPW * nterms; 2 * NT * stp < kDChunks; ++stp) {
+        for (int stp = dstep + 2 * total; 2 * NT * stp < dchunks; ++stp) {
             DCopy<2> dc;
-            dcopy_load<NT>(pd.du64, pd.outD, sBlk, kDChunks, stp, wave, lane, dc);
+            dcopy_load<NT>(pd.du64, pd.outD, sBlk, dchunks, stp, wave, lane, dc);
             dcopy_store(dc, lane);
         }
     }
 }
 
 template <bool WD>
-__device__ __forceinline__ void class_f32_item(const ProblemDesc &pd, int item, int32_t *sTile, int32_t *sBlk,
-                                               int32_t *sTerm, floatx4 *sW, floatx4 *sU) {
+__device__ __forceinline__ void class_f32_item(const ProblemDesc &pd, int item, int part, int parts, int32_t *sTile, int32_t *sBlk,
+                                               int32_t *sTerm, floatx4 *sW, floatx4 *sU, SkipLds &sk) {
     const int groups = pd.mtiles[4 * item + 2];
     if (groups == 0) return;            // an empty slot of a dispatch table
-    if (groups == 4) class_f32_tile<4, WD>(pd, item, sTile, sBlk, sTerm, sW, sU);
-    else if (groups == 2) class_f32_tile<2, WD>(pd, item, sTile, sBlk, sTerm, sW, sU);
-    else class_f32_tile<1, WD>(pd, item, sTile, sBlk, sTerm, sW, sU);
+    auto tile = [&](auto skip) {
+        constexpr bool SKIP = decltype(skip)::value;
+        if (groups == 4) class_f32_tile<4, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+        else if (groups == 2) class_f32_tile<2, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+        else class_f32_tile<1, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+    };
+    if (pd.skip != 0) tile(std::true_type());
+    else tile(std::false_type());
 }
 
 template <bool WD>
@@ -1136,7 +1243,8 @@ void k_class_f32(ProblemDesc pd) {
     __shared__ int32_t sTerm[2 * kMaxClassTerms];     // unique-block pairs of the class
     __shared__ floatx4 sW[4 * 512];                  // staged W, four buffers
     __shared__ floatx4 sU[4 * 512];                  // staged B_IK values, four buffers
-    class_f32_item<WD>(pd, blockIdx.x, sTile, sBlk, sTerm, sW, sU);
+    __shared__ SkipLds sk;
+    class_f32_item<WD>(pd, blockIdx.x, blockIdx.y, gridDim.y, sTile, sBlk, sTerm, sW, sU, sk);
 }
 
 // ---------------------------------------------------------------------------
@@ -1153,23 +1261,25 @@ __global__ __launch_bounds__(64) void k_fill_i32(int32_t *p, int32_t n, int32_t 
 
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_batch_f32(const ProblemDesc *__restrict__ probs, const int32_t *__restrict__ items,
-                 const int32_t *__restrict__ qb, int32_t nq, int32_t *__restrict__ counters) {
+                 const int32_t *__restrict__ qb, int32_t nq, int32_t *__restrict__ counters, int32_t parts) {
     __shared__ int32_t sTile[64 * kTileStride];
     __shared__ int32_t sBlk[128];
     __shared__ int32_t sTerm[2 * kMaxClassTerms];     // unique-block pairs of the class
     __shared__ floatx4 sW[4 * 512];
     __shared__ floatx4 sU[4 * 512];
+    __shared__ SkipLds sk;
     __shared__ int32_t sItem;
     const int home = blockIdx.x % nq;
     int tried = 0;                       // queues found empty (thread 0)
     for (;;) {
-        if (threadIdx.x == 0) sItem = batch_next_item(qb, nq, counters, home, tried);
+        if (threadIdx.x == 0) sItem = batch_next_item(qb, nq, counters, home, tried, parts);
         __syncthreads();
         const int it = __builtin_amdgcn_readfirstlane(sItem);   // uniform: descriptors in scalar registers
         __syncthreads();                 // every thread has read sItem before it changes
         if (it < 0) break;
-        const ProblemDesc pd = probs[items[2 * it]];
-        class_f32_item<false>(pd, items[2 * it + 1], sTile, sBlk, sTerm, sW, sU);
+        const int at = it / parts;
+        const ProblemDesc pd = probs[items[2 * at]];
+        class_f32_item<false>(pd, items[2 * at + 1], it % parts, parts, sTile, sBlk, sTerm, sW, sU, sk);
     }
 }
 
@@ -1243,9 +1353,9 @@ __global__ __launch_bounds__(256) void k_split_ninv(const double *__restrict__ n
 // and step (loaded with one step's loads, stored after the next step's), so
 // that these writes proceed under the contraction's arithmetic; chunks left
 // after the last step are copied at the end of the tile.
-template <int NP, int NI, bool WD>
-__device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item, int32_t *sTile,
-                                                int32_t *sBlk, int32_t *sTerm, u16x8 *sW, floatx4 *sU) {
+template <int NP, int NI, bool WD, bool SKIP>
+__device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item, int part, int parts, int32_t *sTile,
+                                                int32_t *sBlk, int32_t *sTerm, u16x8 *sW, floatx4 *sU, SkipLds &sk) {
     const float *__restrict__ ut32 = pd.ut32;
     double *__restrict__ out = pd.out;
     const int cls = pd.mtiles[4 * item], m0 = pd.mtiles[4 * item + 1];
@@ -1259,7 +1369,7 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     const int nterms = cl.nterms;
     const int32_t *terms = pd.cterms + 2 * cl.term0;
     if (nterms == 0) {
-        empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI);
+        if (part == 0) empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI);
         return;
     }
 
@@ -1275,6 +1385,16 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     }
     if (tid < 2 * nterms) sTerm[tid] = terms[tid];   // unique-block pairs of the class
     __syncthreads();
+    // SKIP false: every term of every row, in order
+    const int quad0 = 16 * part / parts;
+    int total = (16 * (part + 1) / parts - quad0) * nterms;
+    if constexpr (SKIP) total = build_skip<NI>(pd, nterms, part, parts, sTerm, sk, [&](int r, int e, int c) {
+        // the leading parts: exponents of two BF16 values per word, all ones if not finite
+        const uint64_t v = *(const uint64_t *)(pd.w[0] + (int64_t)sTile[r * kTileStride + e] * 64 + 4 * c);
+        uint64_t inf = 0;
+        for (int i = 0; i < 4; ++i) inf |= (v >> (16 * i) & 0x7f80u) == 0x7f80u;
+        return inf == 0;
+    });
 
     // Staging: W is 256 NP chunks of 16 bytes (part c >> 8, row (c & 255) >> 2,
     // chunk c & 3), B_IK of one step 512 chunks (row c >> 3, chunk c & 7).
@@ -1345,10 +1465,12 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
 #pragma unroll
         for (int q = 0; q < NUC; ++q) sU[buf * 512 + udst[q]] = st.u[q];
     };
-    constexpr int kDChunks = 16 * NI * 2048;   // D-hat chunks of the tile
+    // this part's D-hat chunks of the tile, two per thread and step: steps dstep .. dchunks / (2 NT)
+    constexpr int kDSteps = 16 * NI * 2048 / (2 * NT);
+    const int dstep = kDSteps * part / parts, dchunks = kDSteps * (part + 1) / parts * 2 * NT;
 
     doublex4 acc[NI][2];
-    floatx4 part[NI][2];
+    floatx4 psum[NI][2];
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -1361,18 +1483,19 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     // with the addresses the next step needs read meanwhile; (3) the staged
     // operands written to buffer sbuf, and, at the end of a term, a barrier.
     auto step = [&](const Own &oc, int buf, const SAddr &sa, const OAddr &oa, int sbuf, Stage &stn, Own &on,
-                    bool first, bool bar, int nse, int nsh, int noa, int noe, int noh, SAddr &sa_n, OAddr &oa_n,
-                    int stp, DCopy<2> &dprev, auto symt, int ng, int g0, int g1) {
-        constexpr bool S = decltype(symt)::value;
+                    int h, uint32_t on0, uint32_t on1, bool bar, int nse, int nsh, int noa, int noe, int noh, SAddr &sa_n, OAddr &oa_n,
+                    int stp, DCopy<2> &dprev) {
         stage_load(sa, stn);
         own_load(oa, on);
         if constexpr (WD) {
             DCopy<2> dc;
-            dcopy_load<NT>(pd.du64, pd.outD, sBlk, kDChunks, stp, wave, lane, dc);
+            dcopy_load<NT>(pd.du64, pd.outD, sBlk, dchunks, stp, wave, lane, dc);
             dcopy_store(dprev, lane);
             dprev = dc;
         }
         __builtin_amdgcn_sched_barrier(0);
+        const bool any = !SKIP || ((on0 | on1) >> (8 * h) & 255u) != 0;   // some of this wave's products can be nonzero
+        if (any) {
         bf16x8 wf[NI][NP];
 #pragma unroll
         for (int i = 0; i < NI; ++i)
@@ -1381,8 +1504,7 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
                 wf[i][k] = __builtin_bit_cast(bf16x8, sW[((buf * NP + k) * 64 + 16 * i + lr) * 4 + (lk ^ wsw(16 * i + lr))]);
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj) {
-            if (S && jj >= ng) continue;     // symmetric class: this wave's groups of the row
-            const int b = S ? 16 * (jj ? g1 : g0) + lr : 32 * ch + 16 * jj + lr;
+            const int b = 32 * ch + 16 * jj + lr;
             const floatx4 u2a = sU[buf * 512 + b * 8 + ((2 * lk) ^ usw(b))];
             const floatx4 u2b = sU[buf * 512 + b * 8 + ((2 * lk + 1) ^ usw(b))];
             typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -1407,12 +1529,10 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
                 const int qb = NP == 3 ? pb3[pr] : pb2[pr];
 #pragma unroll
                 for (int i = 0; i < NI; ++i)
-                    part[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        wf[i][qa], bfr[qb], (first && pr == 0) ? floatx4{0.f, 0.f, 0.f, 0.f} : part[i][jj], 0, 0, 0);
+                    psum[i][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        wf[i][qa], bfr[qb], (h == 0 && pr == 0) ? floatx4{0.f, 0.f, 0.f, 0.f} : psum[i][jj], 0, 0, 0);
             }
         }
-        sa_n = saddr(nse, nsh);
-        oa_n = oaddr(noa, noe, noh);
         __builtin_amdgcn_sched_group_barrier(0x100, NI * NP + 6 + NWC, 0);   // LDS reads
 #pragma unroll
         for (int x = 0; x < 2 * NPROD * NI; ++x) {
@@ -1420,6 +1540,14 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
             __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);             // two VALU
         }
         __builtin_amdgcn_sched_barrier(0);
+        } else if (h == 0) {                 // the term's sum starts from the second half
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) psum[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+        sa_n = saddr(nse, nsh);
+        oa_n = oaddr(noa, noe, noh);
         stage_store(stn, sbuf);
         if (bar) __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
@@ -1430,78 +1558,55 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     // ends with the only barrier of the term.  Cursors: row index x
     // (a = rw + RP x) and term e; past the last row they repeat (harmless
     // reloads into buffers no step reads).
-    auto next = [&](int cx, int ce, int &nx, int &ne) {
-        ne = ce + 1;
-        nx = cx;
-        if (ne == nterms) {
-            ne = 0;
-            ++nx;
-        }
-        if (nx >= RPW) {
-            nx = cx;
-            ne = ce;
-        }
+    auto entry = [&](int it, int before) {   // before: entry it - 1
+        if constexpr (SKIP) return __builtin_amdgcn_readfirstlane((int)sk.list[min(it, total - 1)]);
+        else if (it == 0) return 256 * quad0;
+        else if (it >= total) return before;
+        else return (before & 255) + 1 < nterms ? before + 1 : (before | 255) + 1;
     };
     Stage s0, s1;
     Own o0, o1;
-    int x = 0, e = 0;
-    int x1, e1;
-    next(0, 0, x1, e1);
+    int c0 = entry(0, 0), c1 = entry(1, c0);   // this iteration and the next
     {
         Stage t0, t1;
-        stage_load(saddr(0, 0), t0);
-        stage_load(saddr(0, 1), t1);
-        own_load(oaddr(rw, 0, 0), o0);
+        stage_load(saddr(c0 & 255, 0), t0);
+        stage_load(saddr(c0 & 255, 1), t1);
+        own_load(oaddr(rw + RP * (c0 >> 8), c0 & 255, 0), o0);
         stage_store(t0, 0);
         stage_store(t1, 1);
     }
-    SAddr sa = saddr(e1, 0);
-    OAddr oa = oaddr(rw, 0, 1);
+    SAddr sa = saddr(c1 & 255, 0);
+    OAddr oa = oaddr(rw + RP * (c0 >> 8), c0 & 255, 1);
     DCopy<2> dpend;                           // D-hat chunks loaded, not yet stored
     dpend.clear();
     __syncthreads();
-    // Symmetric classes (every term pairs a unique block with itself: the
-    // blocks (J, J), with C[a][b] = C[b][a] bit for bit since the products
-    // B[p][a] B[p][b] are the same numbers either way round): row a needs only
-    // the column groups j >= a / 16 (= x / 4, as a = rw + 4 x); the tiles
-    // below the diagonal are written as mirror images.  The groups a row needs
-    // are shared out so that the two waves of a row phase (column halves 0
-    // and 1) do at most two groups each and one each where two are left:
-    // x / 4 = 0: {0, 1} | {2, 3};  1: {1} | {2, 3};  2: {2} | {3};  3: {} | {3}.
-    auto rows = [&](auto symt) {
-        constexpr bool S = decltype(symt)::value;
-        for (int it = 0; it < RPW * nterms; ++it) {
-            next(x, e, x1, e1);
+    // Symmetric classes (the blocks (J, J)) are computed in full here: sharing
+    // out the column groups on and above the diagonal, as the FP32 form does,
+    // cost more (branches inside the step's scheduling regions, code size)
+    // than the skipped groups saved (measured).
+    {
+        for (int it = 0; it < total; ++it) {
+            const int c2 = entry(it + 2, c1);
+            const int x = c0 >> 8, e = c0 & 255, x1 = c1 >> 8, e1 = c1 & 255, e2 = c2 & 255;
             const int a = rw + RP * x, a1 = rw + RP * x1;
-            int x2, e2;
-            next(x1, e1, x2, e2);
-            const int p = x >> 2;
-            int ng = 2, g0 = 2 * ch, g1 = 2 * ch + 1;
-            if constexpr (S) {
-                if (p == 1 && ch == 0) {
-                    ng = 1;
-                    g0 = 1;
-                } else if (p == 2) {
-                    ng = 1;
-                    g0 = 2 + ch;
-                } else if (p == 3) {
-                    ng = ch;
-                    g0 = 3;
-                }
+            uint32_t on0 = 0xffffu, on1 = 0xffffu;
+            if constexpr (SKIP) {
+                const uint32_t rowm = sk.mask[64 * e + a];
+                on0 = __builtin_amdgcn_readfirstlane(rowm & sk.cols[4 * e + 2 * ch]);
+                on1 = __builtin_amdgcn_readfirstlane(rowm & sk.cols[4 * e + 2 * ch + 1]);
             }
             const int ib = 2 * (it & 1), nb = 2 - ib;
-            step(o0, ib, sa, oa, nb, s1, o1, true, false, e1, 1, a1, e1, 0, sa, oa, 2 * it, dpend, symt, ng, g0, g1);
-            step(o1, ib + 1, sa, oa, nb + 1, s0, o0, false, true, e2, 0, a1, e1, 1, sa, oa, 2 * it + 1, dpend, symt,
-                 ng, g0, g1);
+            step(o0, ib, sa, oa, nb, s1, o1, 0, on0, on1, false, e1, 1, a1, e1, 0, sa, oa, dstep + 2 * it, dpend);
+            step(o1, ib + 1, sa, oa, nb + 1, s0, o0, 1, on0, on1, true, e2, 0, a1, e1, 1, sa, oa, dstep + 2 * it + 1, dpend);
+            if (!SKIP || (on0 | on1) != 0) {
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
+                for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    if (!S || j < ng) {
+                    for (int j = 0; j < 2; ++j)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[i][j][v] += (double)part[i][j][v];
-                    }
-            if (e == nterms - 1) {           // end of output row a: store, clear
+                        for (int v = 0; v < 4; ++v) acc[i][j][v] += (double)psum[i][j][v];
+            }
+            if (x1 != x || it + 1 == total) {    // end of output row a: store, clear
 #pragma unroll
                 for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -1511,10 +1616,7 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
                             double *ob = out + (int64_t)blk * kBlockElems;
 #pragma unroll
                             for (int j = 0; j < 2; ++j) {
-                                if (S && j >= ng) continue;
-                                const int G = S ? (j ? g1 : g0) : 2 * ch + j;
-                                __builtin_nontemporal_store(acc[i][j][v], &ob[a * 64 + 16 * G + lr]);
-                                if (S && G > p) ob[(16 * G + lr) * 64 + a] = acc[i][j][v];
+                                __builtin_nontemporal_store(acc[i][j][v], &ob[a * 64 + 32 * ch + 16 * j + lr]);
                             }
                         }
                     }
@@ -1523,19 +1625,15 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
 #pragma unroll
                     for (int j = 0; j < 2; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
             }
-            x = x1;
-            e = e1;
+            c0 = c1;
+            c1 = c2;
         }
-    };
-    // The symmetric sharing of column groups is not used here: its branches
-    // inside the step cost the split-BF16 form more (the step's scheduling
-    // regions, code size) than the skipped groups save (measured).
-    rows(std::false_type());
+    }
     if constexpr (WD) {                  // the last step's chunks, then those past the last step
         dcopy_store(dpend, lane);
-        for (int stp = 2 * RPW * nterms; 2 * NT * stp < kDChunks; ++stp) {
+        for (int stp = dstep + 2 * total; 2 * NT * stp < dchunks; ++stp) {
             DCopy<2> dc;
-            dcopy_load<NT>(pd.du64, pd.outD, sBlk, kDChunks, stp, wave, lane, dc);
+            dcopy_load<NT>(pd.du64, pd.outD, sBlk, dchunks, stp, wave, lane, dc);
             dcopy_store(dc, lane);
         }
     }
@@ -1544,13 +1642,18 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
 // One member tile (item) of one problem; sTile, sBlk, sTerm, sW and sU are the
 // workgroup's LDS tables and staging buffers.
 template <int NP, bool WD>
-__device__ __forceinline__ void class_bf16_item(const ProblemDescB &pd, int item, int32_t *sTile, int32_t *sBlk,
-                                                int32_t *sTerm, u16x8 *sW, floatx4 *sU) {
+__device__ __forceinline__ void class_bf16_item(const ProblemDescB &pd, int item, int part, int parts, int32_t *sTile, int32_t *sBlk,
+                                                int32_t *sTerm, u16x8 *sW, floatx4 *sU, SkipLds &sk) {
     const int groups = pd.mtiles[4 * item + 2];
     if (groups == 0) return;            // an empty slot of a dispatch table
-    if (groups == 4) class_bf16_tile<NP, 4, WD>(pd, item, sTile, sBlk, sTerm, sW, sU);
-    else if (groups == 2) class_bf16_tile<NP, 2, WD>(pd, item, sTile, sBlk, sTerm, sW, sU);
-    else class_bf16_tile<NP, 1, WD>(pd, item, sTile, sBlk, sTerm, sW, sU);
+    auto tile = [&](auto skip) {
+        constexpr bool SKIP = decltype(skip)::value;
+        if (groups == 4) class_bf16_tile<NP, 4, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+        else if (groups == 2) class_bf16_tile<NP, 2, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+        else class_bf16_tile<NP, 1, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+    };
+    if (pd.skip != 0) tile(std::true_type());
+    else tile(std::false_type());
 }
 
 template <int NP, bool WD>
@@ -1561,7 +1664,8 @@ void k_class_bf16(ProblemDescB pd) {
     __shared__ int32_t sTerm[2 * kMaxClassTerms];     // unique-block pairs of the class
     __shared__ u16x8 sW[4 * NP * 64 * 4];            // staged W, four buffers
     __shared__ floatx4 sU[4 * 512];                  // staged B_IK values, four buffers
-    class_bf16_item<NP, WD>(pd, blockIdx.x, sTile, sBlk, sTerm, sW, sU);
+    __shared__ SkipLds sk;
+    class_bf16_item<NP, WD>(pd, blockIdx.x, blockIdx.y, gridDim.y, sTile, sBlk, sTerm, sW, sU, sk);
 }
 
 // Many problems in one persistent launch, split BF16 (the queues and their
@@ -1569,23 +1673,25 @@ void k_class_bf16(ProblemDescB pd) {
 template <int NP>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_batch_bf16(const ProblemDescB *__restrict__ probs, const int32_t *__restrict__ items,
-                  const int32_t *__restrict__ qb, int32_t nq, int32_t *__restrict__ counters) {
+                  const int32_t *__restrict__ qb, int32_t nq, int32_t *__restrict__ counters, int32_t parts) {
     __shared__ int32_t sTile[64 * kTileStride];
     __shared__ int32_t sBlk[128];
     __shared__ int32_t sTerm[2 * kMaxClassTerms];
     __shared__ u16x8 sW[4 * NP * 64 * 4];
     __shared__ floatx4 sU[4 * 512];
+    __shared__ SkipLds sk;
     __shared__ int32_t sItem;
     const int home = blockIdx.x % nq;
     int tried = 0;                       // queues found empty (thread 0)
     for (;;) {
-        if (threadIdx.x == 0) sItem = batch_next_item(qb, nq, counters, home, tried);
+        if (threadIdx.x == 0) sItem = batch_next_item(qb, nq, counters, home, tried, parts);
         __syncthreads();
         const int it = __builtin_amdgcn_readfirstlane(sItem);   // uniform: descriptors in scalar registers
         __syncthreads();                 // every thread has read sItem before it changes
         if (it < 0) break;
-        const ProblemDescB pd = probs[items[2 * it]];
-        class_bf16_item<NP, false>(pd, items[2 * it + 1], sTile, sBlk, sTerm, sW, sU);
+        const int at = it / parts;
+        const ProblemDescB pd = probs[items[2 * at]];
+        class_bf16_item<NP, false>(pd, items[2 * at + 1], it % parts, parts, sTile, sBlk, sTerm, sW, sU, sk);
     }
 }
 
@@ -1668,6 +1774,14 @@ static unsigned f64_parts(int64_t tiles) {
     return parts;
 }
 
+// The same for the FP32 and split-BF16 forms, one workgroup per CU: BF16x6 with
+// D-hat at lmax 100 (about 100 tiles) 349 -> 117 us.
+static unsigned tile_parts(int64_t tiles) {
+    unsigned parts = 1;
+    while (parts < 8 && tiles * parts < 512) parts *= 2;
+    return parts;
+}
+
 hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st) {
     if (a.nblocks == 0) return hipSuccess;
     if (prec == 0) {
@@ -1686,16 +1800,17 @@ hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st) {
         hipLaunchKernelGGL(k_ninv_f32, dim3((unsigned)((a.npix + 255) / 256)), dim3(256), 0, st, a.ninv,
                            a.npix, a.wf32);
         ProblemDesc pd{a.mtiles, a.classes, a.class_terms, a.class_blk, a.class_itab, a.ut32, a.wf32, a.out,
-                       a.du64, a.blk_uid, a.outD};
-        if (a.outD) hipLaunchKernelGGL(k_class_f32<true>, dim3((unsigned)a.nmtiles), dim3(512), 0, st, pd);
-        else hipLaunchKernelGGL(k_class_f32<false>, dim3((unsigned)a.nmtiles), dim3(512), 0, st, pd);
+                       a.du64, a.blk_uid, a.outD, a.masks.units, a.masks.cols, a.masks.overflow, a.skip};
+        if (a.outD) hipLaunchKernelGGL(k_class_f32<true>, dim3((unsigned)a.nmtiles, tile_parts(a.nmtiles)), dim3(512), 0, st, pd);
+        else hipLaunchKernelGGL(k_class_f32<false>, dim3((unsigned)a.nmtiles, tile_parts(a.nmtiles)), dim3(512), 0, st, pd);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_split_ninv, dim3((unsigned)((a.npix + 255) / 256)), dim3(256), 0, st, a.ninv,
                        a.npix, a.wsplit[0], a.wsplit[1], a.wsplit[2]);
-    const dim3 grid((unsigned)a.nmtiles);
+    const dim3 grid((unsigned)a.nmtiles, tile_parts(a.nmtiles));
     ProblemDescB pd{a.mtiles, a.classes, a.class_terms, a.class_blk, a.class_itab, a.ut32,
-                    {a.wsplit[0], a.wsplit[1], a.wsplit[2]}, a.out, a.du64, a.blk_uid, a.outD};
+                    {a.wsplit[0], a.wsplit[1], a.wsplit[2]}, a.out, a.du64, a.blk_uid, a.outD,
+                    a.masks.units, a.masks.cols, a.masks.overflow, a.skip};
     if (a.outD) {
         if (prec == 2) hipLaunchKernelGGL((k_class_bf16<2, true>), grid, dim3(512), 0, st, pd);
         else hipLaunchKernelGGL((k_class_bf16<3, true>), grid, dim3(512), 0, st, pd);
@@ -1738,17 +1853,18 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t st) {
     if (b.persistent) {
         if (b.nitems > 0) {
             const dim3 g((unsigned)b.nworkgroups);
+            const int32_t parts = (int32_t)tile_parts(b.nitems);
             if (!bf16)
-                hipLaunchKernelGGL(k_batch_f32, g, dim3(512), 0, st, b.desc, b.items, b.qb, b.nq, b.counters);
+                hipLaunchKernelGGL(k_batch_f32, g, dim3(512), 0, st, b.desc, b.items, b.qb, b.nq, b.counters, parts);
             else if (b.prec == 2)
-                hipLaunchKernelGGL(k_batch_bf16<2>, g, dim3(512), 0, st, b.descb, b.items, b.qb, b.nq, b.counters);
+                hipLaunchKernelGGL(k_batch_bf16<2>, g, dim3(512), 0, st, b.descb, b.items, b.qb, b.nq, b.counters, parts);
             else
-                hipLaunchKernelGGL(k_batch_bf16<3>, g, dim3(512), 0, st, b.descb, b.items, b.qb, b.nq, b.counters);
+                hipLaunchKernelGGL(k_batch_bf16<3>, g, dim3(512), 0, st, b.descb, b.items, b.qb, b.nq, b.counters, parts);
         }
     } else {
         for (int p = 0; p < b.nprob; ++p) {
             if (b.ngtiles[p] == 0) continue;
-            const dim3 g((unsigned)b.ngtiles[p]);
+            const dim3 g((unsigned)b.ngtiles[p], tile_parts(b.ngtiles[p]));
             if (!bf16) {
                 ProblemDesc d = b.host_desc[p];
                 d.mtiles = b.gtiles[p];
