@@ -136,6 +136,8 @@ __host__ __forceinline__ int order_workgroups(int L) {
     return (L + 1 + g - 1) / g * g;
 }
 
+constexpr int kRowChunk = 512;       // degrees of a row staged at once (a multiple of the 64-degree chunks)
+
 struct Deg4 { double v[4]; };   // four consecutive degrees of a row (32-byte aligned)
 
 __device__ __forceinline__ Deg4 deg4(const double *p) { return *(const Deg4 *)p; }
@@ -144,7 +146,8 @@ __device__ __forceinline__ Deg4 deg4(const double *p) { return *(const Deg4 *)p;
 // Legendre synthesis.  Workgroup m; thread t takes the ring pairs t + 256 q
 // (R of them at a time, interleaved for latency).  Degrees go four at a time
 // (even, odd, even, odd i), the next four read ahead; the rescale test is made
-// once per four degrees (four steps grow |mu| by less than 2.5).
+// once per four degrees (four steps grow |mu| by less than 2.5; staged rows:
+// eight degrees, less than 6).
 // ---------------------------------------------------------------------------
 template <int R>
 __global__ __launch_bounds__(kLegThreads) void k_leg_syn(ShtDesc d, const int64_t *__restrict__ row_off,
@@ -158,7 +161,14 @@ __global__ __launch_bounds__(kLegThreads) void k_leg_syn(ShtDesc d, const int64_
     const int L = d.lmax, nl = L - m + 1;
     const int64_t off = row_off[m];
     const double *b = rb + off, *kk = rk + off, *cc = ac + off, *cs = as + off;
-    for (int rp0 = threadIdx.x; rp0 < d.nhalf; rp0 += kLegThreads * R) {
+    // One or two ring pairs per thread do too little work per degree to hide
+    // the uniform loads' latency: there the row's values pass through LDS,
+    // kRowChunk degrees at a time, read by all lanes at once (L = 255: 19.6 ->
+    // 15.2 us).
+    constexpr bool STAGED = R <= 2;
+    __shared__ double row[STAGED ? 3 : 1][STAGED ? kRowChunk + 4 : 1];
+    for (int rp1 = 0; rp1 < d.nhalf; rp1 += kLegThreads * R) {
+        const int rp0 = rp1 + (int)threadIdx.x;
         double ct[R], mu[R], mup[R], ec[R], es[R], oc[R], os[R];
         int e[R];
 #pragma unroll
@@ -170,9 +180,36 @@ __global__ __launch_bounds__(kLegThreads) void k_leg_syn(ShtDesc d, const int64_
             e[q] = d.lmm_exp[(int64_t)m * d.nhalf + rp];
             ec[q] = es[q] = oc[q] = os[q] = 0.0;
         }
-        Deg4 gb = deg4(b), gc = deg4(cc), gs = deg4(cs);
+        Deg4 gb, gc, gs;
+        if constexpr (!STAGED) {
+            gb = deg4(b);
+            gc = deg4(cc);
+            gs = deg4(cs);
+        }
         for (int i0 = 0; i0 < nl; i0 += 4) {
-            const Deg4 nb = deg4(b + i0 + 4), nc = deg4(cc + i0 + 4), ns = deg4(cs + i0 + 4);
+            Deg4 nb, nc, ns;
+            if constexpr (STAGED) {
+                const int j0 = i0 & (kRowChunk - 1);
+                if (j0 == 0) {               // the row's next chunk; entries past it are its zero padding
+                    __syncthreads();         // the previous chunk is used up
+                    for (int t = threadIdx.x; t < min(kRowChunk, nl - i0) + 4; t += kLegThreads) {
+                        row[0][t] = b[i0 + t];
+                        row[1][t] = cc[i0 + t];
+                        row[2][t] = cs[i0 + t];
+                    }
+                    __syncthreads();
+                    gb = deg4(row[0]);
+                    gc = deg4(row[1]);
+                    gs = deg4(row[2]);
+                }
+                nb = deg4(row[0] + j0 + 4);
+                nc = deg4(row[1] + j0 + 4);
+                ns = deg4(row[2] + j0 + 4);
+            } else {
+                nb = deg4(b + i0 + 4);
+                nc = deg4(cc + i0 + 4);
+                ns = deg4(cs + i0 + 4);
+            }
             if (i0 != 0 && (i0 & 63) == 0) {      // chunk start: carry K of the chunk before
                 const double sk = kk[i0 - 1];
 #pragma unroll
@@ -186,7 +223,8 @@ __global__ __launch_bounds__(kLegThreads) void k_leg_syn(ShtDesc d, const int64_
             bool grow = false;
 #pragma unroll
             for (int q = 0; q < R; ++q) grow |= fabs(mu[q]) > kBig;
-            if (__builtin_expect(__any(grow), 0)) {
+            // (staged rows: every eight degrees)
+            if ((!STAGED || (i0 & 4) == 0) && __builtin_expect(__any(grow), 0)) {
 #pragma unroll
                 for (int q = 0; q < R; ++q) {
                     if (fabs(mu[q]) > kBig) {
@@ -266,14 +304,13 @@ __device__ __forceinline__ RingG ring_g(const ShtDesc &d, const double *gbuf, in
 // up to six ring pairs per thread fit in 128 VGPRs (four waves per SIMD; the
 // few values the compiler then keeps in scratch are read only on the rare
 // reload path)
-template <int T, int R>
-__global__ __launch_bounds__(T, R <= 6 ? 4 : 1) void k_leg_adj(ShtDesc d, const int64_t *__restrict__ row_off,
+template <int T, int R, int CH>
+__global__ __launch_bounds__(T, R > 6 ? 1 : CH > 8 ? 2 : 4) void k_leg_adj(ShtDesc d, const int64_t *__restrict__ row_off,
                                                          const double *__restrict__ rb,
                                                          const double *__restrict__ rk,
                                                          const double *__restrict__ gbuf,
                                                          double *__restrict__ ac, double *__restrict__ as) {
-    constexpr int CH = 8;
-    constexpr int LPR = T / 16;          // lanes summing one of the 16 values
+    constexpr int LPR = T / (2 * CH);    // lanes summing one of the 2 CH values
     __shared__ double sRed[2 * CH * T];
     const int m = order_of_workgroup(d.lmax);
     if (m < 0) return;
@@ -294,9 +331,21 @@ __global__ __launch_bounds__(T, R <= 6 ? 4 : 1) void k_leg_adj(ShtDesc d, const 
         mup[q] = ok ? d.lmm_mant[(int64_t)m * d.nhalf + r] : 0.0;
         g[q] = ring_g(d, gbuf, r, m, e[q]);
     }
-    Deg4 b0 = deg4(b), b1 = deg4(b + 4);
+    constexpr bool AHEAD = CH == 8;      // read a pass ahead; longer passes would need too many scalar registers
+    Deg4 bb[CH / 4];
+    if constexpr (AHEAD) {
+        bb[0] = deg4(b);
+        bb[1] = deg4(b + 4);
+    }
     for (int i0 = 0; i0 < nl; i0 += CH) {
-        const Deg4 n0 = deg4(b + i0 + 8), n1 = deg4(b + i0 + 12);
+        Deg4 n0, n1;
+        if constexpr (AHEAD) {
+            n0 = deg4(b + i0 + 8);
+            n1 = deg4(b + i0 + 12);
+        } else {
+#pragma unroll
+            for (int q = 0; q < CH / 4; ++q) bb[q] = deg4(b + min(i0 + 4 * q, (nl + 3) & ~3));   // zeros past the row
+        }
         if (i0 != 0 && (i0 & 63) == 0) {
             const double sk = kk[i0 - 1];
 #pragma unroll
@@ -337,7 +386,7 @@ __global__ __launch_bounds__(T, R <= 6 ? 4 : 1) void k_leg_adj(ShtDesc d, const 
             double x = mu[q], xp = mup[q];
 #pragma unroll
             for (int j = 0; j < CH; ++j) {
-                const double bj = j < 4 ? b0.v[j] : b1.v[j - 4];
+                const double bj = bb[j / 4].v[j & 3];
                 const double xn = fma(ct[q], x, -bj * xp);
                 vc[j] = fma(xn, (j & 1) ? g[q].mc : g[q].pc, vc[j]);
                 vs[j] = fma(xn, (j & 1) ? g[q].ms : g[q].ps, vs[j]);
@@ -356,7 +405,7 @@ __global__ __launch_bounds__(T, R <= 6 ? 4 : 1) void k_leg_adj(ShtDesc d, const 
         const int row = threadIdx.x / LPR, seg = threadIdx.x % LPR;
         double sum = 0.0;
 #pragma unroll
-        for (int t = 0; t < 16; ++t) sum += sRed[row * T + t * LPR + seg];
+        for (int t = 0; t < 2 * CH; ++t) sum += sRed[row * T + t * LPR + seg];
 #pragma unroll
         for (int o = LPR / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
         if (seg == 0) {
@@ -368,8 +417,10 @@ __global__ __launch_bounds__(T, R <= 6 ? 4 : 1) void k_leg_adj(ShtDesc d, const 
             }
         }
         __syncthreads();
-        b0 = n0;
-        b1 = n1;
+        if constexpr (AHEAD) {
+            bb[0] = n0;
+            bb[1] = n1;
+        }
     }
 }
 
@@ -703,9 +754,12 @@ hipError_t sht_adjoint(const ShtDesc &d, const double *map, double *gbuf, double
     });
     // every ring pair in one pass: 128 threads with up to 8 ring pairs each
     // (half the partial sums of 256 threads), else 256 threads with 6 or 8
+    // One or two ring pairs per thread: a pass is bound by the latency of its
+    // loads, LDS and barriers, and 16 degrees share them (32 were slower: 25
+    // against 20 us at L = 255).
     auto adj = [&](auto t, auto r) {
-        constexpr int T = decltype(t)::value, R = decltype(r)::value;
-        hipLaunchKernelGGL((k_leg_adj<T, R>), dim3(order_workgroups(L)), dim3(T), 0, st, d, d.row_off, d.rec_b, d.rec_k, gbuf, ac,
+        constexpr int T = decltype(t)::value, R = decltype(r)::value, CH = R <= 2 ? 16 : 8;
+        hipLaunchKernelGGL((k_leg_adj<T, R, CH>), dim3(order_workgroups(L)), dim3(T), 0, st, d, d.row_off, d.rec_b, d.rec_k, gbuf, ac,
                            as);
     };
     using T128 = std::integral_constant<int, 128>;
