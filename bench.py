@@ -353,6 +353,23 @@ def cpu_baseline_batch(probs, budget_s, sampled):
     return res, gates
 
 
+def cut_share(fwhm_pix, two_hop=False):
+    """Share of a contraction's 2 64^3 products per term that the radial cut
+    (three FWHM) does not make zero, on flat tiles of 8 x 8 unit pixels: row p
+    in the middle tile, columns a and b in its 3 x 3 neighbours (in neighbouring
+    tiles unless two_hop).  Rooflines count these products only: the kernels
+    leave out most of the others, so their count is no bound."""
+    x, y = (v.ravel() for v in np.meshgrid(np.arange(-8, 16), np.arange(-8, 16), indexing="ij"))
+    tx, ty = x // 8, y // 8
+    own = (tx == 0) & (ty == 0)
+    near = ((x[own, None] - x) ** 2 + (y[own, None] - y) ** 2 <= (3.0 * fwhm_pix) ** 2).astype(np.float64)
+    pairs = near.T @ near / 64.0
+    if two_hop:
+        return float(pairs.mean())
+    stored = (np.abs(tx[:, None] - tx) <= 1) & (np.abs(ty[:, None] - ty) <= 1)
+    return float(pairs[stored].mean())
+
+
 def copy_calibration(torch, nbytes):
     """One plain device copy of nbytes (read and written), launched first so
     that counter runs can scale FETCH_SIZE / WRITE_SIZE by a known size."""
@@ -384,7 +401,7 @@ def run_batch(args):
         pr["ninv_dev"] = torch.as_tensor(pr["ninv"]).cuda()
         pr["out"] = torch.empty(pr["g"].out_len, dtype=torch.float64, device="cuda")
     nelem = sum(pr["g"].nblocks for pr in probs) * 4096
-    alg_flop = sum(2.0 * 64 ** 3 * pr["g"].nterms for pr in probs)
+    alg_flop = sum(2.0 * 64 ** 3 * pr["g"].nterms * cut_share(pr["prob"]["fwhm_pix"]) for pr in probs)
     modes = [m.strip() for m in args.modes.split(",") if m.strip()]
     # sampled rows, two per problem: the first tile and a random one
     rng = np.random.default_rng(11)
@@ -872,7 +889,7 @@ def run_two_hop(args):
     out = torch.empty(nblk * 4096, dtype=torch.float64, device="cuda")
     stream = torch.cuda.current_stream()
     nelem = nblk * 4096
-    alg_flop = 2.0 * 64 ** 3 * nterms
+    alg_flop = 2.0 * 64 ** 3 * nterms * cut_share(cfg.fwhm_pix, two_hop=True)
     print(f"# two-hop {args.config} {prec}: lmax={cfg.lmax} blocks={nblk} (one-hop {g.nblocks}) terms={nterms} "
           f"output={nelem * 8 / 1e9:.1f} GB pattern_setup={setup:.2f}s", file=sys.stderr, flush=True)
 
@@ -994,7 +1011,7 @@ def run_two_grid(args):
     out = torch.empty(x.out_len, dtype=torch.float64, device="cuda")
     stream = torch.cuda.current_stream()
     nelem = x.nblocks * 4096
-    alg_flop = 2.0 * 64 ** 3 * x.nterms
+    alg_flop = 2.0 * 64 ** 3 * x.nterms * cut_share(cfg.fwhm_pix)
     print(f"# two-grid {args.config}: lmax1={cfg.lmax} lmax2={lmax2} npix2={g2.npix} blocks={x.nblocks} "
           f"terms={x.nterms} (max {x.max_terms}) unique={x.nunique} setup={setup:.2f}s", file=sys.stderr, flush=True)
 
@@ -1102,7 +1119,7 @@ def main():
     out_D = torch.empty(g.out_len, dtype=torch.float64, device="cuda")
     stream = torch.cuda.current_stream()
     nelem = g.nblocks * 4096
-    alg_flop = 2.0 * 64 ** 3 * g.nterms
+    alg_flop = 2.0 * 64 ** 3 * g.nterms * cut_share(cfg.fwhm_pix)
     print(f"# workload {args.config}: lmax={cfg.lmax} npix={g.npix} nblocks={g.nblocks} "
           f"nterms={g.nterms} nunique={g.nunique} grid_setup={setup_grid:.2f}s", file=sys.stderr, flush=True)
     # block-rows whose outputs are kept for the comparison with the oracle

@@ -487,6 +487,9 @@ __device__ __forceinline__ F64Lds f64_lds(char *p, int S) {
 // One 16-byte load per lane straight into LDS: lane l's value goes to byte lds +
 // 16 l (uniform lds).  Counted in vmcnt; the compiler knows of neither, so the
 // waits are written out where the staged data change hands.
+// It writes m0, which the compiler does not let an asm name as clobbered: nothing
+// else in these kernels uses it (LDS instructions do not on gfx950, and no
+// register array is indexed by a variable).
 __device__ __forceinline__ void load_to_lds(const void *src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(src) : "memory");
 }
