@@ -163,7 +163,7 @@ struct sympix_kernel {
     float *ut32 = nullptr;
     double *u64t = nullptr;
     sympix::UnitMasks masks = {};
-    bool short_cut = false;
+    double cut_spacings = 0.0;   // the radial cut in mean pixel spacings (0: none)
     void *block = nullptr;    // one stream-ordered allocation holding all of the above
 };
 
@@ -447,7 +447,7 @@ sympix_status sample_btnb(const sympix_grid *g, const sympix_kernel *d, const sy
     a.u64t = b->u64t;
     a.ut32 = b->ut32;
     a.masks = b->masks;
-    a.skip = b->short_cut ? 1 : 0;
+    a.skip = sympix::short_cut(prec, b->cut_spacings) ? 1 : 0;
     if (pat) {
         const DevClasses *dc = nullptr;
         s = two_hop_tables(g, b->device, &pat, &dc);
@@ -510,7 +510,7 @@ sympix_status tabulate(const TabSource &src, const sympix_grid *g, const sympix_
         kr->y_cut = 2.0 * sr * sr;
         if (kr->y_cut < y_dom) y_dom = kr->y_cut;
     }
-    kr->short_cut = sympix::short_cut(radius, std::sqrt(4.0 * kPi / (double)src.npix));
+    kr->cut_spacings = radius > 0 ? radius / std::sqrt(4.0 * kPi / (double)src.npix) : 0.0;
     // nodes uniform in s = sqrt(y) up to the domain end plus a little slack for
     // device rounding of y; the last interval keeps one spare node
     const double s_top = std::fmax(std::sqrt(y_dom) * (1.0 + 1e-6), 1e-300);
@@ -1138,12 +1138,12 @@ sympix_status sympix_batch_create(const sympix_problem *p, int32_t n, int32_t pr
             sympix::ProblemDesc d{dtiles, dg->classes, dg->class_terms, dg->class_blk, dg->class_itab,
                                   p[i].b->ut32, nullptr, p[i].out_dev, nullptr, nullptr, nullptr,
                                   p[i].b->masks.units, p[i].b->masks.cols, p[i].b->masks.overflow,
-                                  p[i].b->short_cut ? 1 : 0};
+                                  sympix::short_cut(prec, p[i].b->cut_spacings) ? 1 : 0};
             bt->hdesc[t].push_back(d);
             sympix::ProblemDescB db{dtiles, dg->classes, dg->class_terms, dg->class_blk, dg->class_itab,
                                     p[i].b->ut32, {nullptr, nullptr, nullptr}, p[i].out_dev, nullptr, nullptr, nullptr,
                                     p[i].b->masks.units, p[i].b->masks.cols, p[i].b->masks.overflow,
-                                    p[i].b->short_cut ? 1 : 0};
+                                    sympix::short_cut(prec, p[i].b->cut_spacings) ? 1 : 0};
             bt->hdescb[t].push_back(db);
             const int64_t nmt = (int64_t)tiles.size() / 4;
             const std::vector<int32_t> &gt = t == SYMPIX_TILES_64 ? geo.cls.gtiles : geo.cls.gtiles32;
@@ -1558,7 +1558,7 @@ sympix_status sympix_sample_BtNB_cross(const sympix_cross *c, const sympix_kerne
     a.u64t = b->u64t;
     a.ut32 = b->ut32;
     a.masks = b->masks;
-    a.skip = b->short_cut ? 1 : 0;
+    a.skip = sympix::short_cut(prec, b->cut_spacings) ? 1 : 0;
     a.classes = dx->classes;
     a.class_terms = dx->class_terms;
     a.class_blk = dx->class_blk;

@@ -86,19 +86,24 @@ struct BtnbArgs {
     double *out;
     UnitMasks masks;          // of the unique blocks u64t / ut32
     int32_t max_terms;        // most terms of a class
-    int32_t skip;             // the kernel's cut is short_cut
+    int32_t skip;             // the kernel's cut is a short_cut in this precision
     // optional D-hat blocks written by the same launch:
     // stored block n gets unique block blk_uid[n] of du64 (row-major FP64)
     const double *du64;
     const int32_t *blk_uid;
     double *outD;             // nullptr: B-hat^T N^-1 B-hat only
 };
-// Whether a radial cut is short enough for the FP32 and split-BF16 forms to test
-// their MFMAs against the masks.  Measured, lmax 1500, every MFMA / tests: FP32
-// cut at 9 mean pixel spacings 7.00 / 5.55 ms, at 15 6.99 / 7.37 (the two lines
-// cross near 13.5); BF16x6 4.92 / 4.40 and 5.15 / 5.21.  (The FP64 form tests at
-// every cut: 23.6 -> 21.8 ms at 15 spacings, lmax 2048.)
-inline bool short_cut(double radius, double spacing) { return radius > 0 && radius < 12.5 * spacing; }
+// Whether a radial cut, in mean pixel spacings (0: none), is short enough for a
+// form of the contraction (prec: 1 FP32, 2 or 3 BF16 parts) to test its MFMAs
+// against the masks.  Measured at lmax 1500, every MFMA / tests.  FP32: cut at 9
+// spacings 7.00 / 5.55 ms, at 15 6.99 / 7.37, the lines cross near 13; BF16x6: at
+// 9 4.81 / 4.44 ms, at 12 4.97 / 5.03, with D-hat at 9 5.86 / 5.58, at 10.8 5.99 /
+// 6.07; BF16x3: at 9 3.21 / 3.22, at 12 3.38 / 3.56, at lmax 480 already 0.549 /
+// 0.556 at 9.  (The FP64 form tests at every cut: 23.6 -> 21.8 ms at 15 spacings,
+// lmax 2048.)
+inline bool short_cut(int prec, double spacings) {
+    return spacings > 0 && spacings < (prec == 1 ? 12.5 : prec == 3 ? 10.0 : 8.0);
+}
 hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st);
 
 // Operands of the FP64 class GEMM (device pointers).
