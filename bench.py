@@ -644,8 +644,9 @@ def run_factor(args):
     f_ms = np.array([ev[2 * i].elapsed_time(ev[2 * i + 1]) for i in range(args.steps)])
     s_ms = np.array([ev[2 * i + 1].elapsed_time(ev[2 * i + 2]) for i in range(args.steps)])
     ms_step = wall * 1000.0 / args.steps
-    f_bytes = g.ntiles * (3 * 4096 * 8 + 4)            # D_JJ and C_JJ read, U_J written, info
-    s_bytes = g.ntiles * 4096 * 8 + 2 * 8 * g.npix      # U read, r read, x written
+    tri = 160 * 128                                     # the 128-byte lines that hold part of an upper triangle
+    f_bytes = g.ntiles * (2 * tri + 4096 * 8 + 4)       # D_JJ and C_JJ read, U_J written, info
+    s_bytes = g.ntiles * tri + 2 * 8 * g.npix           # U read, r read, x written
     f_gbs = f_bytes / (f_ms.mean() * 1e-3) / 1e9
     s_gbs = s_bytes / (s_ms.mean() * 1e-3) / 1e9
     info_h = info.cpu().numpy()

@@ -27,7 +27,7 @@ def sample(g, kern, ninv, prec):
     return out.view(g.nblocks, 64, 64)
 
 
-@pytest.mark.parametrize("lmax,fwhm", [(40, 0.25), (40, 2.0), (64, 1.0), (64, 5.0), (100, 2.5), (64, None)])
+@pytest.mark.parametrize("lmax,fwhm", [(40, 0.25), (40, 2.0), (64, 1.0), (64, 5.0), (100, 2.5), (64, 2.9), (64, 3.6), (64, None)])
 def test_cut_widths(lmax, fwhm):
     """Cut radii (3 FWHM, in mean pixel spacings) from under one pixel to none."""
     g, og = sp.Grid(lmax, 8), G.make_grid(lmax, 8)
