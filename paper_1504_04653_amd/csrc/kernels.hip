@@ -493,12 +493,15 @@ __device__ __forceinline__ F64Lds f64_lds(char *p, int S) {
 __device__ __forceinline__ void load_to_lds(const void *src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(src) : "memory");
 }
-// The same with a uniform address and a byte offset per lane.
+// The same with a uniform address and a byte offset per lane.  A vector memory
+// instruction may read a scalar register that a vector instruction wrote (the
+// address comes from v_readfirstlane) only five wait states later; the compiler
+// does not see the load, so the asm brings all five (s_mov one, s_nop 3 four).
 __device__ __forceinline__ void load_to_lds(const void *uniform_src, uint32_t offset, uint32_t lds) {
     const uint64_t p = (uint64_t)(uintptr_t)uniform_src;
     const uint64_t src = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)p) |
                          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(p >> 32)) << 32;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(offset), "s"(src) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(offset), "s"(src) : "memory");
 }
 
 // Every load but the N youngest memory operations done, and LDS traffic too;
