@@ -374,10 +374,10 @@ __device__ __forceinline__ void dcopy_store(const DCopy<N> &dc, int lane) {
 // zero.  The workgroup clears the member tile's blocks (and gives them their
 // D-hat copies), without LDS; the caller returns right after.
 template <int NT, bool WD, class PD>
-__device__ __forceinline__ void empty_class_tile(const PD &pd, const DevClass &cl, int m0, int rows) {
+__device__ __forceinline__ void empty_class_tile(const PD &pd, const DevClass &cl, int m0, int rows, int tid) {
     constexpr int kChunks = kBlockElems / 2;            // 16-byte chunks of a block
     const int nm = min(rows, cl.nblocks - m0);
-    for (int c = threadIdx.x; c < nm * kChunks; c += NT) {
+    for (int c = tid; c < nm * kChunks; c += NT) {
         const int m = c / kChunks, q = c - m * kChunks;
         const int64_t blk = pd.cblk[cl.blk0 + m0 + m];
         __builtin_nontemporal_store(doublex2{0.0, 0.0}, (doublex2 *)(pd.out + blk * kBlockElems) + q);
@@ -516,20 +516,19 @@ __device__ __forceinline__ bool not_finite(double v) {
 }
 
 template <int NI, bool WD>
-__device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item, int part, int parts, const F64Lds &lds) {
+__device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item, int part, int parts, int tid, const F64Lds &lds) {
     constexpr int R = f64_rows(NI);
     const double *__restrict__ ut = pd.u64t;
     const double *__restrict__ wv = pd.w;
     double *__restrict__ out = pd.out;
     const int cls = pd.mtiles[4 * item], m0 = pd.mtiles[4 * item + 1];
     const DevClass cl = pd.classes[cls];
-    const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, lr = lane & 15, lk = lane >> 4;
     const int nterms = cl.nterms;
     const int32_t *terms = pd.cterms + 2 * cl.term0;
     if (nterms == 0) {
-        if (part == 0) empty_class_tile<256, WD>(pd, cl, m0, 16 * NI);
+        if (part == 0) empty_class_tile<256, WD>(pd, cl, m0, 16 * NI, tid);
         return;
     }
 
@@ -837,9 +836,9 @@ void k_class_f64(ProblemDesc64 pd) {
     const int item = blockIdx.x;        // pd.mtiles: a dispatch table, slot per workgroup
     const int groups = pd.mtiles[4 * item + 2];
     if (groups == 0) return;            // an empty slot
-    if (groups == 4) class_f64_tile<4, WD>(pd, item, blockIdx.y, gridDim.y, lds);
-    else if (groups == 2) class_f64_tile<2, WD>(pd, item, blockIdx.y, gridDim.y, lds);
-    else class_f64_tile<1, WD>(pd, item, blockIdx.y, gridDim.y, lds);
+    if (groups == 4) class_f64_tile<4, WD>(pd, item, blockIdx.y, gridDim.y, threadIdx.x, lds);
+    else if (groups == 2) class_f64_tile<2, WD>(pd, item, blockIdx.y, gridDim.y, threadIdx.x, lds);
+    else class_f64_tile<1, WD>(pd, item, blockIdx.y, gridDim.y, threadIdx.x, lds);
 }
 
 // Queue draining shared by the persistent batch kernels: thread 0 takes the
@@ -859,6 +858,19 @@ __device__ __forceinline__ int batch_next_item(const int32_t *__restrict__ qb, i
         ++tried;
     }
     return it;
+}
+
+// The thread's index where a kernel loops over work items, opaque to the
+// compiler: what a tile's body derives from it (swizzles, staging offsets, of
+// every tile height and form) would otherwise be computed once ahead of the
+// loop and held in registers through all bodies, which spilled (104 to 256
+// bytes per lane).  Four levels from lmax 512 down, without / with it: BF16x6
+// at beams of 2.5 pixels 1542 / 1506 us, at 5 pixels 1694 / 1620; BF16x3 1132 /
+// 1100 and 1160 / 1115; FP64 at 5 pixels 3523 / 3496.
+__device__ __forceinline__ int thread_index() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
 }
 
 // a10 in FP64: the FP64 class GEMM of many problems in one persistent launch
@@ -882,10 +894,10 @@ void k_batch_f64(const ProblemDesc64 *__restrict__ probs, const int32_t *__restr
         const int at = it / parts, part = it % parts;
         const ProblemDesc64 pd = probs[items[2 * at]];
         const int item = items[2 * at + 1];
-        const int groups = pd.mtiles[4 * item + 2];
-        if (groups == 4) class_f64_tile<4, false>(pd, item, part, parts, lds);
-        else if (groups == 2) class_f64_tile<2, false>(pd, item, part, parts, lds);
-        else class_f64_tile<1, false>(pd, item, part, parts, lds);
+        const int groups = pd.mtiles[4 * item + 2], tid = thread_index();
+        if (groups == 4) class_f64_tile<4, false>(pd, item, part, parts, tid, lds);
+        else if (groups == 2) class_f64_tile<2, false>(pd, item, part, parts, tid, lds);
+        else class_f64_tile<1, false>(pd, item, part, parts, tid, lds);
     }
 }
 
@@ -923,9 +935,9 @@ struct SkipLds {
 // the row quads of this part of the tile are listed.  Returns the length of the
 // list.
 template <int NI, class PD, class Finite>
-__device__ __forceinline__ int build_skip(const PD &pd, int nterms, int part, int parts, const int32_t *sTerm, SkipLds &sk,
+__device__ __forceinline__ int build_skip(const PD &pd, int nterms, int part, int parts, int tid, const int32_t *sTerm, SkipLds &sk,
                                           const Finite &w_finite) {
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int lane = tid & 63;
     for (int x = tid; x < 32 * nterms; x += 512)
         ((uint32_t *)sk.mask)[x] = ((const uint32_t *)pd.units)[(int64_t)sTerm[2 * (x >> 5)] * 32 + (x & 31)];
     for (int x = tid; x < 4 * nterms; x += 512) sk.cols[x] = pd.unit_cols[(int64_t)sTerm[2 * (x >> 2) + 1] * 4 + (x & 3)];
@@ -981,21 +993,20 @@ __global__ __launch_bounds__(256) void k_ninv_f32(const double *__restrict__ nin
 // 512 threads of the workgroup take part.  sTile / sBlk / sTerm are the
 // workgroup's LDS tables, sW / sU its four staging buffers.
 template <int NI, bool WD, bool SKIP>
-__device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, int part, int parts, int32_t *sTile,
+__device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, int part, int parts, int tid, int32_t *sTile,
                                                int32_t *sBlk, int32_t *sTerm, floatx4 *sW, floatx4 *sU, SkipLds &sk) {
     const float *__restrict__ ut32 = pd.ut32;
     double *__restrict__ out = pd.out;
     constexpr int NW = 8, NT = 64 * NW, RP = NW / 2, RPW = 64 / RP;
     const int cls = pd.mtiles[4 * item], m0 = pd.mtiles[4 * item + 1];
     const DevClass cl = pd.classes[cls];
-    const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rw = wave % RP, ch = wave / RP;          // row phase, column half
     const int lane = tid & 63, lr = lane & 15, lk = lane >> 4;
     const int nterms = cl.nterms;
     const int32_t *terms = pd.cterms + 2 * cl.term0;
     if (nterms == 0) {
-        if (part == 0) empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI);
+        if (part == 0) empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI, tid);
         return;
     }
 
@@ -1014,7 +1025,7 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     // SKIP false: every term of every row, in order
     const int quad0 = 16 * part / parts;
     int total = (16 * (part + 1) / parts - quad0) * nterms;
-    if constexpr (SKIP) total = build_skip<NI>(pd, nterms, part, parts, sTerm, sk, [&](int r, int e, int c) {
+    if constexpr (SKIP) total = build_skip<NI>(pd, nterms, part, parts, tid, sTerm, sk, [&](int r, int e, int c) {
         const floatx4 v = *(const floatx4 *)(pd.wf + (int64_t)sTile[r * kTileStride + e] * 64 + 4 * c);
         return fabsf(v[0]) < INFINITY && fabsf(v[1]) < INFINITY && fabsf(v[2]) < INFINITY && fabsf(v[3]) < INFINITY;
     });
@@ -1252,15 +1263,15 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
 }
 
 template <bool WD>
-__device__ __forceinline__ void class_f32_item(const ProblemDesc &pd, int item, int part, int parts, int32_t *sTile, int32_t *sBlk,
+__device__ __forceinline__ void class_f32_item(const ProblemDesc &pd, int item, int part, int parts, int tid, int32_t *sTile, int32_t *sBlk,
                                                int32_t *sTerm, floatx4 *sW, floatx4 *sU, SkipLds &sk) {
     const int groups = pd.mtiles[4 * item + 2];
     if (groups == 0) return;            // an empty slot of a dispatch table
     auto tile = [&](auto skip) {
         constexpr bool SKIP = decltype(skip)::value;
-        if (groups == 4) class_f32_tile<4, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
-        else if (groups == 2) class_f32_tile<2, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
-        else class_f32_tile<1, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+        if (groups == 4) class_f32_tile<4, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
+        else if (groups == 2) class_f32_tile<2, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
+        else class_f32_tile<1, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
     };
     if (pd.skip != 0) tile(std::true_type());
     else tile(std::false_type());
@@ -1275,7 +1286,7 @@ void k_class_f32(ProblemDesc pd) {
     __shared__ floatx4 sW[4 * 512];                  // staged W, four buffers
     __shared__ floatx4 sU[4 * 512];                  // staged B_IK values, four buffers
     __shared__ SkipLds sk;
-    class_f32_item<WD>(pd, blockIdx.x, blockIdx.y, gridDim.y, sTile, sBlk, sTerm, sW, sU, sk);
+    class_f32_item<WD>(pd, blockIdx.x, blockIdx.y, gridDim.y, threadIdx.x, sTile, sBlk, sTerm, sW, sU, sk);
 }
 
 // ---------------------------------------------------------------------------
@@ -1310,7 +1321,7 @@ void k_batch_f32(const ProblemDesc *__restrict__ probs, const int32_t *__restric
         if (it < 0) break;
         const int at = it / parts;
         const ProblemDesc pd = probs[items[2 * at]];
-        class_f32_item<false>(pd, items[2 * at + 1], it % parts, parts, sTile, sBlk, sTerm, sW, sU, sk);
+        class_f32_item<false>(pd, items[2 * at + 1], it % parts, parts, thread_index(), sTile, sBlk, sTerm, sW, sU, sk);
     }
 }
 
@@ -1365,6 +1376,12 @@ __global__ __launch_bounds__(256) void k_split_ninv(const double *__restrict__ n
     w2[i] = bf16_bits((float)(r1 - (double)bf16_value(m)));
 }
 
+// Of three values by value: an index into the descriptor's array would keep the
+// descriptor of a batch problem in scratch memory.
+__device__ __forceinline__ const uint16_t *one_of(int k, const uint16_t *a, const uint16_t *b, const uint16_t *c) {
+    return k == 0 ? a : k == 1 ? b : c;
+}
+
 // Split-BF16 class GEMM (the decomposition of the FP32 form above): W = N^-1
 // split into NP BF16 parts, M = B_IJ[p][a] B_IK[p][b] formed as an FP32
 // product and split into NP parts in registers; NP = 3 keeps the products hh,
@@ -1385,13 +1402,12 @@ __global__ __launch_bounds__(256) void k_split_ninv(const double *__restrict__ n
 // that these writes proceed under the contraction's arithmetic; chunks left
 // after the last step are copied at the end of the tile.
 template <int NP, int NI, bool WD, bool SKIP>
-__device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item, int part, int parts, int32_t *sTile,
+__device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item, int part, int parts, int tid, int32_t *sTile,
                                                 int32_t *sBlk, int32_t *sTerm, u16x8 *sW, floatx4 *sU, SkipLds &sk) {
     const float *__restrict__ ut32 = pd.ut32;
     double *__restrict__ out = pd.out;
     const int cls = pd.mtiles[4 * item], m0 = pd.mtiles[4 * item + 1];
     const DevClass cl = pd.classes[cls];
-    const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int NW = 8, NT = 64 * NW;              // waves, threads
     constexpr int RP = NW / 2, RPW = 64 / RP;          // row phases, rows per wave
@@ -1400,7 +1416,7 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     const int nterms = cl.nterms;
     const int32_t *terms = pd.cterms + 2 * cl.term0;
     if (nterms == 0) {
-        if (part == 0) empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI);
+        if (part == 0) empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI, tid);
         return;
     }
 
@@ -1419,7 +1435,7 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     // SKIP false: every term of every row, in order
     const int quad0 = 16 * part / parts;
     int total = (16 * (part + 1) / parts - quad0) * nterms;
-    if constexpr (SKIP) total = build_skip<NI>(pd, nterms, part, parts, sTerm, sk, [&](int r, int e, int c) {
+    if constexpr (SKIP) total = build_skip<NI>(pd, nterms, part, parts, tid, sTerm, sk, [&](int r, int e, int c) {
         // the leading parts: exponents of two BF16 values per word, all ones if not finite
         const uint64_t v = *(const uint64_t *)(pd.w[0] + (int64_t)sTile[r * kTileStride + e] * 64 + 4 * c);
         uint64_t inf = 0;
@@ -1444,7 +1460,7 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
         int c = tid + NT * r;
         if (c >= 256 * NP) c -= 256;
         const int k = __builtin_amdgcn_readfirstlane(c >> 8), q = c & 255, row = q >> 2, sub = q & 3;
-        wsrc[r] = pd.w[k] + 8 * sub;
+        wsrc[r] = one_of(k, pd.w[0], pd.w[1], pd.w[2]) + 8 * sub;
         wrow[r] = min(row, 16 * NI - 1) * kTileStride;
         // LDS layouts, in 16-byte chunks: W row r (64 bytes) keeps its chunk c at
         // 4 r + (c ^ wsw(r)), a B_IK row b (128 bytes) its chunk c at 8 b + (c ^
@@ -1679,15 +1695,15 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
 // One member tile (item) of one problem; sTile, sBlk, sTerm, sW and sU are the
 // workgroup's LDS tables and staging buffers.
 template <int NP, bool WD>
-__device__ __forceinline__ void class_bf16_item(const ProblemDescB &pd, int item, int part, int parts, int32_t *sTile, int32_t *sBlk,
+__device__ __forceinline__ void class_bf16_item(const ProblemDescB &pd, int item, int part, int parts, int tid, int32_t *sTile, int32_t *sBlk,
                                                 int32_t *sTerm, u16x8 *sW, floatx4 *sU, SkipLds &sk) {
     const int groups = pd.mtiles[4 * item + 2];
     if (groups == 0) return;            // an empty slot of a dispatch table
     auto tile = [&](auto skip) {
         constexpr bool SKIP = decltype(skip)::value;
-        if (groups == 4) class_bf16_tile<NP, 4, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
-        else if (groups == 2) class_bf16_tile<NP, 2, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
-        else class_bf16_tile<NP, 1, WD, SKIP>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+        if (groups == 4) class_bf16_tile<NP, 4, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
+        else if (groups == 2) class_bf16_tile<NP, 2, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
+        else class_bf16_tile<NP, 1, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
     };
     if (pd.skip != 0) tile(std::true_type());
     else tile(std::false_type());
@@ -1702,7 +1718,7 @@ void k_class_bf16(ProblemDescB pd) {
     __shared__ u16x8 sW[4 * NP * 64 * 4];            // staged W, four buffers
     __shared__ floatx4 sU[4 * 512];                  // staged B_IK values, four buffers
     __shared__ SkipLds sk;
-    class_bf16_item<NP, WD>(pd, blockIdx.x, blockIdx.y, gridDim.y, sTile, sBlk, sTerm, sW, sU, sk);
+    class_bf16_item<NP, WD>(pd, blockIdx.x, blockIdx.y, gridDim.y, threadIdx.x, sTile, sBlk, sTerm, sW, sU, sk);
 }
 
 // Many problems in one persistent launch, split BF16 (the queues and their
@@ -1728,7 +1744,7 @@ void k_batch_bf16(const ProblemDescB *__restrict__ probs, const int32_t *__restr
         if (it < 0) break;
         const int at = it / parts;
         const ProblemDescB pd = probs[items[2 * at]];
-        class_bf16_item<NP, false>(pd, items[2 * at + 1], it % parts, parts, sTile, sBlk, sTerm, sW, sU, sk);
+        class_bf16_item<NP, false>(pd, items[2 * at + 1], it % parts, parts, thread_index(), sTile, sBlk, sTerm, sW, sU, sk);
     }
 }
 
