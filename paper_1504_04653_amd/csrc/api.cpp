@@ -466,6 +466,7 @@ sympix_status sample_btnb(const sympix_grid *g, const sympix_kernel *d, const sy
     }
     a.nmtiles = (int64_t)ct.gtiles.size() / 4;
     a.max_terms = ct.max_class_terms;
+    a.tile_rows = 64;
     a.nblocks = nblocks;
     a.npix = geo.npix;
     a.ninv = ninv_dev;
@@ -1133,7 +1134,7 @@ sympix_status sympix_batch_create(const sympix_problem *p, int32_t n, int32_t pr
             const std::vector<int32_t> &tiles = t == SYMPIX_TILES_64 ? geo.cls.mtiles : geo.cls.mtiles32;
             sympix::ProblemDesc64 d64{dtiles, dg->classes, dg->class_terms, dg->class_blk, dg->class_itab,
                                       p[i].b->u64t, p[i].ninv_dev, p[i].out_dev, nullptr, nullptr, nullptr,
-                                      p[i].b->masks.units, p[i].b->masks.cols, p[i].b->masks.overflow, bt->max_terms};
+                                      p[i].b->masks.units, p[i].b->masks.cols, p[i].b->masks.overflow, bt->max_terms, 64};
             bt->hdesc64[t].push_back(d64);
             sympix::ProblemDesc d{dtiles, dg->classes, dg->class_terms, dg->class_blk, dg->class_itab,
                                   p[i].b->ut32, nullptr, p[i].out_dev, nullptr, nullptr, nullptr,
@@ -1344,6 +1345,7 @@ struct DevCross {
     int32_t *class_blk = nullptr;
     int32_t *class_itab = nullptr;
     int32_t *gtiles = nullptr;          // dispatch table of the class-grid launch
+    int32_t *gtiles32 = nullptr;        // that of an FP64 launch on tiles of at most 32 rows, where it takes them
     int32_t *exp_items = nullptr;
     int32_t *exp_blk = nullptr;
 };
@@ -1357,6 +1359,7 @@ void free_dev_cross(DevCross &d) {
     hipFree(d.class_blk);
     hipFree(d.class_itab);
     hipFree(d.gtiles);
+    hipFree(d.gtiles32);
     hipFree(d.exp_items);
     hipFree(d.exp_blk);
     d = DevCross();
@@ -1410,6 +1413,8 @@ sympix_status cross_tables(const sympix_cross *c, int device, const DevCross **o
     if (e == hipSuccess) e = upload(&d.class_blk, x.cls.class_blk.data(), x.cls.class_blk.size());
     if (e == hipSuccess) e = upload(&d.class_itab, x.cls.class_itab.data(), x.cls.class_itab.size());
     if (e == hipSuccess) e = upload(&d.gtiles, x.cls.gtiles.data(), x.cls.gtiles.size());
+    if (e == hipSuccess && sympix::f64_tile_rows(x.cls.max_class_terms) == 32)
+        e = upload(&d.gtiles32, x.cls.gtiles32.data(), x.cls.gtiles32.size());
     if (e == hipSuccess) e = upload(&d.exp_items, x.exp_items.data(), x.exp_items.size());
     if (e == hipSuccess) e = upload(&d.exp_blk, x.exp_blk.data(), x.exp_blk.size());
     if (e != hipSuccess) {
@@ -1563,9 +1568,10 @@ sympix_status sympix_sample_BtNB_cross(const sympix_cross *c, const sympix_kerne
     a.class_terms = dx->class_terms;
     a.class_blk = dx->class_blk;
     a.class_itab = dx->class_itab;
-    a.mtiles = dx->gtiles;
-    a.nmtiles = (int64_t)x.cls.gtiles.size() / 4;
     a.max_terms = x.cls.max_class_terms;
+    a.tile_rows = prec == SYMPIX_FP64 ? sympix::f64_tile_rows(a.max_terms) : 64;
+    a.mtiles = a.tile_rows == 64 ? dx->gtiles : dx->gtiles32;
+    a.nmtiles = (int64_t)(a.tile_rows == 64 ? x.cls.gtiles : x.cls.gtiles32).size() / 4;
     a.nblocks = nblocks;
     a.npix = g2.npix;
     a.ninv = ninv2_dev;

@@ -86,6 +86,7 @@ struct BtnbArgs {
     double *out;
     UnitMasks masks;          // of the unique blocks u64t / ut32
     int32_t max_terms;        // most terms of a class
+    int32_t tile_rows;        // most members of a tile of mtiles: 64 or 32 (FP64 alone)
     int32_t skip;             // the kernel's cut is a short_cut in this precision
     // optional D-hat blocks written by the same launch:
     // stored block n gets unique block blk_uid[n] of du64 (row-major FP64)
@@ -120,6 +121,7 @@ struct ProblemDesc64 {
     const uint16_t *units, *unit_cols;   // UnitMasks of u64t
     const int32_t *overflow;
     int32_t max_terms;        // most terms a class of the launch has
+    int32_t tile_rows;        // most members a tile of the launch has: 64 or 32
 };
 
 // Operands of the split-BF16 class GEMM (device pointers).

@@ -146,6 +146,25 @@ struct CrossGeometry {
 // takes them from a table in one global largest-first order (geometry.cpp).
 constexpr int64_t kShortLaunchTiles = 32 * 256;
 
+// LDS of a workgroup of the FP64 contraction (the tile of its kernel says what
+// lies there), whose classes have up to `terms` terms, on tiles of up to `rows`
+// members.  Its steps are listed 16 terms (64 pixel groups) at a time, so that
+// the lists do not grow with the terms, of which two grids have up to 128.
+constexpr int kListSteps = 64;
+constexpr int f64_stage_bytes(int rows) { return (rows + 64 + 16) * 128; }
+constexpr int f64_lds_bytes(int terms, int rows) {
+    return 3 * f64_stage_bytes(rows) + 4 * 192 + 2 * (64 + 4) * terms + (2 + 4) * 12 * kListSteps +
+           4 * (2 * terms + rows * (terms | 1));
+}
+
+// Members per tile of an FP64 launch.  Two workgroups share a CU (alone, one
+// reaches two thirds of their rate), so each has half its 160 KiB of LDS: with
+// 64 members a class may have up to 51 terms (two grids pass that where the
+// auxiliary one has more than twice the band limit), with 32 up to 121.  With
+// lists of whole row groups 37 was the most: lmax 256 with 589 (49 terms), beams
+// of 5 pixels, took 7.96 ms, now 5.58; without a cut 8.53, now 6.21.
+constexpr int f64_tile_rows(int terms) { return terms > 51 ? 32 : 64; }
+
 // Status codes follow sympix_status. On failure err holds a message.
 int build_geometry(int32_t lmax, int32_t k, double margin, Geometry &g, std::string &err);
 

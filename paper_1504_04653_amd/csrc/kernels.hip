@@ -445,41 +445,35 @@ __device__ __forceinline__ void empty_class_tile(const PD &pd, const DevClass &c
 // accumulators busy (and lie in the phase).
 __host__ __device__ constexpr int f64_rows(int ni) { return ni == 4 ? 4 : 8; }
 __host__ __device__ constexpr int f64_sym_rows(int ni, int jlo) { return jlo == 3 ? 4 : jlo == 2 ? (ni == 4 ? 2 : 4) : ni == 4 ? 1 : 2; }
-constexpr int kLastStep = 0x8000;
+constexpr int kLastStep = 0x8000, kLastOfRows = 0x4000;   // the last step of a list, of a row group
 
-// LDS of an FP64 class tile, sized by the most terms S a class of the launch
-// has.  The staging buffers come first: three of kStage bytes, holding W (64
-// rows of 128 bytes), B_IK (64 columns) and B_IJ (16 rows).
-constexpr int kStageU2 = 64 * 128, kStageU1 = 2 * 64 * 128, kStage = kStageU1 + 16 * 128;
-
+// LDS of an FP64 class tile, f64_lds_bytes(S, rows) of it for up to S terms per
+// class and `rows` members per tile.  The staging buffers come first: three,
+// holding W (64 rows of 128 bytes, 32 in tiles of fewer members), B_IK (64
+// columns) and B_IJ (16 rows).
 struct F64Lds {
     char *stage;
     int32_t *blk;               // [192]: stored block per member row; its D-hat source block; and the stored
                                 // blocks again, at 16 i + 4 lk + v that of row 16 i + lk + 4 v
     uint16_t *mask;             // [64 * S]: units of (term, row a) in which B_IJ is not all zero
     uint16_t *cols;             // [4 * S]: units of (term, column group j) in which B_IK is not all zero
-    uint32_t *on;               // [4][3][4 * S]: per wave, steps of three row groups: bit 4 q + t for MFMA t of accumulator q
-    uint16_t *code;             // [4][3][4 * S]: 4 term + pixel group of these steps, the last with kLastStep
+    uint32_t *on;               // [4][3][kListSteps]: per wave, three lists' steps: bit 4 q + t for MFMA t of accumulator q
+    uint16_t *code;             // [4][3][kListSteps]: 4 term + pixel group of these steps, and kLastStep, kLastOfRows
     int32_t *term;              // [2 * S]: unique-block pairs of the class
-    int32_t *tile;              // [64 * stride]: tile I of (member row, term)
-    int stride, terms;          // terms: S
+    int32_t *tile;              // [rows * stride]: tile I of (member row, term)
+    int stride;
 };
 
-__host__ __device__ constexpr int f64_lds_bytes(int S) {
-    return 3 * kStage + 4 * 192 + 2 * (64 + 4 + 48) * S + 4 * (48 * S + 2 * S + 64 * (S | 1));
-}
-
-__device__ __forceinline__ F64Lds f64_lds(char *p, int S) {
+__device__ __forceinline__ F64Lds f64_lds(char *p, int S, int rows) {
     F64Lds l;
     l.stage = p;
-    l.blk = (int32_t *)(p + 3 * kStage);
+    l.blk = (int32_t *)(p + 3 * f64_stage_bytes(rows));
     l.mask = (uint16_t *)(l.blk + 192);          // 8-byte aligned, as cols: read four at a time
     l.cols = l.mask + 64 * S;
     l.code = l.cols + 4 * S;
-    l.term = (int32_t *)(l.code + 48 * S);
+    l.term = (int32_t *)(l.code + 12 * kListSteps);
     l.on = (uint32_t *)(l.term + 2 * S);
-    l.tile = (int32_t *)(l.on + 48 * S);
-    l.terms = S;
+    l.tile = (int32_t *)(l.on + 12 * kListSteps);
     l.stride = S | 1;                        // odd: rows fall on different banks
     return l;
 }
@@ -518,6 +512,8 @@ __device__ __forceinline__ bool not_finite(double v) {
 template <int NI, bool WD>
 __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item, int part, int parts, int tid, const F64Lds &lds) {
     constexpr int R = f64_rows(NI);
+    constexpr int kWRows = NI == 4 ? 64 : 32;    // rows of W staged
+    constexpr int kStageU2 = kWRows * 128, kStageU1 = kStageU2 + 64 * 128, kStage = f64_stage_bytes(kWRows);
     const double *__restrict__ ut = pd.u64t;
     const double *__restrict__ wv = pd.w;
     double *__restrict__ out = pd.out;
@@ -525,7 +521,7 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
     const DevClass cl = pd.classes[cls];
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, lr = lane & 15, lk = lane >> 4;
-    const int nterms = cl.nterms;
+    const int nterms = __builtin_amdgcn_readfirstlane(cl.nterms);
     const int32_t *terms = pd.cterms + 2 * cl.term0;
     if (nterms == 0) {
         if (part == 0) empty_class_tile<256, WD>(pd, cl, m0, 16 * NI, tid);
@@ -572,7 +568,7 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
     constexpr int kRows[4] = {4 * f64_sym_rows(NI, 0), 4 * f64_sym_rows(NI, 1), 4 * f64_sym_rows(NI, 2), 4 * f64_sym_rows(NI, 3)};
     constexpr int kFirst[5] = {0, 16 / kRows[0], 16 / kRows[0] + 16 / kRows[1], 16 / kRows[0] + 16 / kRows[1] + 16 / kRows[2],
                                16 / kRows[0] + 16 / kRows[1] + 16 / kRows[2] + 16 / kRows[3]};
-    const bool sym = cl.sym != 0;
+    const bool sym = __builtin_amdgcn_readfirstlane(cl.sym) != 0;
     auto phase_of = [&](int g) { return !sym || g < kFirst[1] ? 0 : g < kFirst[2] ? 1 : g < kFirst[3] ? 2 : 3; };
     auto rows_of = [&](int g) { const int p = phase_of(g); return !sym ? R : p == 0 ? kRows[0] : p == 1 ? kRows[1] : p == 2 ? kRows[2] : kRows[3]; };
     auto row0_of = [&](int g) {
@@ -584,61 +580,61 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
     if (part >= parts) return;
     const int g_begin = ng * part / parts, g_end = ng * (part + 1) / parts;   // this workgroup's groups
 
-    // The steps of row group g, and this wave's MFMAs of them, into its lists:
-    // lane 4 e + G looks at pixel group G of term e.  Every wave builds its own
-    // (the steps are the same for all).  At least two steps: the first pixel group
-    // left out fills up, with no MFMA.
-    auto build = [&](int g) __attribute__((always_inline)) {
-        uint16_t *code = lds.code + (3 * wave + g % 3) * 4 * lds.terms;
-        uint32_t *on = lds.on + (3 * wave + g % 3) * 4 * lds.terms;
-        const int a0 = row0_of(g), nr = rows_of(g), jlo = phase_of(g);
-        int n = 0, spare = 0;
-        for (int e0 = 0; e0 < nterms; e0 += 16) {
-            const int e = min(e0 + (lane >> 2), nterms - 1), G = lane & 3;
-            const bool ok = e0 + (lane >> 2) < nterms;
-            // bits 16 j + t of c: column group j; bits 16 r + t of m: row r of four
-            const uint64_t nib = 0x000f000f000f000full;
-            uint64_t c = *(const uint64_t *)(lds.cols + 4 * e) >> (4 * G) & nib;
-            if (jlo > 0) c = c >> (16 * jlo) << (16 * jlo);
-            uint32_t any_c = (uint32_t)c | (uint32_t)(c >> 32), bits = 0, any_m = 0;
-            any_c |= any_c >> 16;
-            if (!sym) {
-                if (wave != 0) c = c >> (16 * wave) | c << (64 - 16 * wave);   // column group (w + r) mod 4 to place r
+    // A unit: 16 terms of a row group.  Its steps, and this wave's MFMAs of them,
+    // into list `slot`: lane l looks at pixel group l & 3 of the unit's term l / 4.
+    // Every wave builds its own (the steps are the same for all).  At least two
+    // steps: the first pixel group left out fills up, with no MFMA.
+    struct Unit { int g, k; };
+    const int units = (nterms + 15) >> 4;        // per row group
+    auto after_unit = [&](const Unit &u) { return u.k + 1 < units ? Unit{u.g, u.k + 1} : Unit{u.g + 1, 0}; };
+    uint16_t *const codes = lds.code + 3 * kListSteps * wave;
+    uint32_t *const ons = lds.on + 3 * kListSteps * wave;
+    auto build = [&](const Unit &u, int slot) __attribute__((always_inline)) {
+        uint16_t *code = codes + kListSteps * slot;
+        uint32_t *on = ons + kListSteps * slot;
+        const int a0 = row0_of(u.g), nr = rows_of(u.g), jlo = phase_of(u.g);
+        const int e0 = 16 * u.k + (lane >> 2), e = min(e0, nterms - 1), G = lane & 3;
+        // bits 16 j + t of c: column group j; bits 16 r + t of m: row r of four
+        const uint64_t nib = 0x000f000f000f000full;
+        uint64_t c = *(const uint64_t *)(lds.cols + 4 * e) >> (4 * G) & nib;
+        if (jlo > 0) c = c >> (16 * jlo) << (16 * jlo);
+        uint32_t any_c = (uint32_t)c | (uint32_t)(c >> 32), bits = 0, any_m = 0;
+        any_c |= any_c >> 16;
+        if (!sym) {
+            if (wave != 0) c = c >> (16 * wave) | c << (64 - 16 * wave);   // column group (w + r) mod 4 to place r
 #pragma unroll
-                for (int r = 0; r < R; r += 4) {
-                    const uint64_t m = *(const uint64_t *)(lds.mask + 64 * e + a0 + r) >> (4 * G) & nib, x = m & c;
-                    any_m |= (uint32_t)m | (uint32_t)(m >> 32);
-                    const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
-                    bits |= ((lo | lo >> 12) & 255u | ((hi | hi >> 12) & 255u) << 8) << (4 * r);
-                }
-            } else {
-                const int nj = 4 - jlo;
-                for (int r = 0; r < nr; r += 4) {
-                    const uint64_t m = *(const uint64_t *)(lds.mask + 64 * e + a0 + r) >> (4 * G) & nib;
-                    any_m |= (uint32_t)m | (uint32_t)(m >> 32);
-                    const uint32_t own = (uint32_t)(m >> (16 * wave)) & 15u;
-                    for (int j = jlo; j < 4; ++j) bits |= (own & (uint32_t)(c >> (16 * j))) << (4 * (r / 4 * nj + j - jlo));
-                }
+            for (int r = 0; r < R; r += 4) {
+                const uint64_t m = *(const uint64_t *)(lds.mask + 64 * e + a0 + r) >> (4 * G) & nib, x = m & c;
+                any_m |= (uint32_t)m | (uint32_t)(m >> 32);
+                const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
+                bits |= (((lo | lo >> 12) & 255u) | ((hi | hi >> 12) & 255u) << 8) << (4 * r);
             }
-            any_m |= any_m >> 16;
-            const bool any = (any_m & any_c & 15u) != 0;
-            const uint64_t in_b = __ballot(ok && any), out_b = __ballot(ok && !any);
-            if (ok && any) {
-                const int i = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(in_b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in_b, 0));
-                code[i] = (uint16_t)(4 * e + G);
-                on[i] = bits;
+        } else {
+            const int nj = 4 - jlo;
+            for (int r = 0; r < nr; r += 4) {
+                const uint64_t m = *(const uint64_t *)(lds.mask + 64 * e + a0 + r) >> (4 * G) & nib;
+                any_m |= (uint32_t)m | (uint32_t)(m >> 32);
+                const uint32_t own = (uint32_t)(m >> (16 * wave)) & 15u;
+                for (int j = jlo; j < 4; ++j) bits |= (own & (uint32_t)(c >> (16 * j))) << (4 * (r / 4 * nj + j - jlo));
             }
-            n += __popcll(in_b);
-            if (out_b) spare = 4 * e0 + (__ffsll((unsigned long long)out_b) - 1);
+        }
+        any_m |= any_m >> 16;
+        const bool in = e0 < nterms && (any_m & any_c & 15u) != 0;
+        const uint64_t in_b = __ballot(in);
+        const int n = __popcll(in_b), first = kListSteps * u.k;   // code of lane 0: 4 term + pixel group
+        const int end = kLastStep | (u.k + 1 == units ? kLastOfRows : 0);
+        if (in) {
+            const int i = __builtin_amdgcn_mbcnt_hi((uint32_t)(in_b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in_b, 0));
+            code[i] = (uint16_t)((first + lane) | (i > 0 && i == n - 1 ? end : 0));
+            on[i] = bits;
         }
         if (lane < 2 - n) {
-            code[n + lane] = (uint16_t)spare;
+            code[n + lane] = (uint16_t)((first + __ffsll((unsigned long long)~in_b) - 1) | (n + lane == 1 ? end : 0));
             on[n + lane] = 0;
         }
         // read by other lanes of this wave
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        if (lane == 0) code[max(n, 2) - 1] |= kLastStep;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
 
@@ -646,20 +642,20 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
     // a column of B_IK, a row of B_IJ) keeps its 16-byte chunk c (pixels 8 (c /
     // 2) + 2 (c mod 2) and the next of the group's) at 8 r + (c ^ (r & 7)), so
     // that the eight lanes of a read phase fall on different banks.  Wave w
-    // loads rows 16 w + 8 k + lane / 8 (k = 0, 1) of W and B_IK, and half of the
-    // rows of B_IJ.  Rows past the tile repeat its last member, rows past the
-    // group its own (no wave reads them).
+    // loads rows 16 w + 8 k + lane / 8 (k = 0, 1) of W (8 w + lane / 8 of 32)
+    // and B_IK, and half of the rows of B_IJ.  Rows past the tile repeat its last
+    // member, rows past the group its own (no wave reads them).
     const int lrow = lane >> 3, lchunk = (lane & 7) ^ lrow;
     const int lpix = 8 * (lchunk >> 1) + 2 * (lchunk & 1);
-    const int wrow0 = min(16 * wave + lrow, 16 * NI - 1) * lds.stride;
-    const int wrow1 = min(16 * wave + 8 + lrow, 16 * NI - 1) * lds.stride;
+    const int wrow0 = min(kWRows / 4 * wave + lrow, 16 * NI - 1) * lds.stride;
+    const int wrow1 = min(16 * wave + 8 + lrow, 16 * NI - 1) * lds.stride;      // (kWRows 64)
     const uint32_t stage0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds.stage;
-    constexpr int kLoads = 5;            // per wave and step
+    constexpr int kLoads = NI == 4 ? 5 : 4;      // per wave and step
     // where a step (g, code) finds its operands: its term's unique blocks, and this lane's tiles I
     struct Src { int g, code, tile0, tile1, uid1, uid2; };
     auto source = [&](int g, int code) __attribute__((always_inline)) {
-        const int e = (code & ~kLastStep) >> 2;
-        return Src{g, code, lds.tile[wrow0 + e], lds.tile[wrow1 + e], lds.term[2 * e], lds.term[2 * e + 1]};
+        const int e = (code & (kLastOfRows - 1)) >> 2;
+        return Src{g, code, lds.tile[wrow0 + e], NI == 4 ? lds.tile[wrow1 + e] : 0, lds.term[2 * e], lds.term[2 * e + 1]};
     };
     const uint32_t off2 = 8 * (lrow * 64 + lpix);                     // lane offsets into B_IK and B_IJ
     const uint32_t off1 = 8 * (((8 * (wave & 1) + lrow) & (R - 1)) * 64 + lpix);
@@ -673,8 +669,8 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
                     sym ? 8 * (((8 * (wave & 1) + lrow) & (rows_of(q.g) - 1)) * 64 + lpix) : off1};
     };
     auto stage = [&](const Addr &q, uint32_t at) __attribute__((always_inline)) {
-        load_to_lds(q.w0, at + 2048 * wave);
-        load_to_lds(q.w1, at + 2048 * wave + 1024);
+        load_to_lds(q.w0, at + 32 * kWRows * wave);
+        if constexpr (NI == 4) load_to_lds(q.w1, at + 2048 * wave + 1024);
         load_to_lds(q.u2, off2, at + kStageU2 + 2048 * wave);
         load_to_lds(q.u2 + 8 * 64, off2, at + kStageU2 + 2048 * wave + 1024);
         load_to_lds(q.u1, q.off1, at + kStageU1 + 1024 * (wave & 1));   // two waves write the same
@@ -684,22 +680,31 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
         return *(const doublex2 *)(rows + 128 * r + 16 * ((2 * lk + h) ^ (r & 7)));
     };
 
-    // Steps in order: step s of group g with code c is followed by step s + 1, or
-    // if it is the last by the next group's first; past the last group it
-    // repeats (its loads go where no step reads).
-    struct Cursor { int g, s; };
+    // Steps in order: a step of group g at place `at` of the lists is followed by
+    // the next place, or if it is its list's last by the next list's first; past
+    // the last group it repeats (its loads go where no step reads).
+    struct Cursor { int g, at; };
     auto after = [&](const Cursor &c, int code) __attribute__((always_inline)) {
-        return !(code & kLastStep) ? Cursor{c.g, c.s + 1} : c.g + 1 < g_end ? Cursor{c.g + 1, 0} : c;
+        if (!(code & kLastStep)) return Cursor{c.g, c.at + 1};
+        const int g = (code & kLastOfRows) ? c.g + 1 : c.g, at = (c.at & -kListSteps) + kListSteps;
+        return g < g_end ? Cursor{g, at == 3 * kListSteps ? 0 : at} : c;
     };
-    auto code_at = [&](const Cursor &c) __attribute__((always_inline)) { return (int)lds.code[(3 * wave + c.g % 3) * 4 * lds.terms + c.s]; };
-    auto on_at = [&](const Cursor &c) __attribute__((always_inline)) { return (int)lds.on[(3 * wave + c.g % 3) * 4 * lds.terms + c.s]; };
+    auto code_at = [&](const Cursor &c) __attribute__((always_inline)) { return (int)codes[c.at]; };
+    auto on_at = [&](const Cursor &c) __attribute__((always_inline)) { return (int)ons[c.at]; };
     auto uniform = [&](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
 
     constexpr int kDChunks = 16 * NI * 2048;   // D-hat chunks of the tile
     int stp = kDChunks / 512 * part / parts;   // steps done, counted from the first of this part's chunks
     const int dchunks = kDChunks / 512 * (part + 1) / parts * 512;
     DCopy<2> dpend;
-    for (int g = g_begin; g < min(g_begin + 2, g_end); ++g) build(g);
+    Unit next_unit{g_begin, 0};          // the next to be listed, and where
+    int slot = 0;
+    for (; slot < 3 && next_unit.g < g_end; ++slot) {
+        build(next_unit, slot);
+        next_unit = after_unit(next_unit);
+    }
+    slot = 0;
+    bool begun = false;                  // past the first unit
     int code0, code1, code2, code3;
     uint32_t on;                         // on: this wave's MFMAs of this step
     Cursor c1, c2, c3;                   // the next three steps
@@ -709,7 +714,6 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
         on = uniform(on_at(c0));
         c1 = after(c0, code0);
         code1 = uniform(code_at(c1));
-        if (g_begin + 2 < g_end) build(g_begin + 2);
         c2 = after(c1, code1);
         code2 = uniform(code_at(c2));
         c3 = after(c2, code2);
@@ -727,13 +731,19 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
         auto row = [&](int q) { return SYM ? wave + 4 * (q / NJ) : q; };
         auto col = [&](int q) { return SYM ? JLO + q % NJ : (wave + q) & 3; };
         for (int g = max(gb, g_begin); g < min(ge, g_end); ++g) {
-            if (g > g_begin && g + 2 < g_end) build(g + 2);   // its place held group g - 1's
             const int a0 = row0_of(g);
             doublex4 acc[NR * NJ][NI];
 #pragma unroll
             for (int q = 0; q < NR * NJ; ++q)
 #pragma unroll
                 for (int i = 0; i < NI; ++i) acc[q][i] = doublex4{0.0, 0.0, 0.0, 0.0};
+            for (bool done = false; !done;) {
+            if (begun && next_unit.g < g_end) {      // listed two units ahead, in the place of the one just done
+                build(next_unit, slot);
+                next_unit = after_unit(next_unit);
+                slot = slot == 2 ? 0 : slot + 1;
+            }
+            begun = true;
             for (bool last = false; !last;) {
                 // read now, used after the MFMAs: what the loads of three steps on need, the code of the step
                 // after that, the next step's masks
@@ -769,6 +779,7 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
                 }
                 const Addr ad = addresses(src);
                 last = (code0 & kLastStep) != 0;
+                done = (code0 & kLastOfRows) != 0;
                 c1 = c2;
                 c2 = c3;
                 c3 = c4;
@@ -782,6 +793,7 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
                 if constexpr (WD) dcopy_store(dpend, lane);
                 stage(ad, stage0 + at);
                 at = at == 2 * kStage ? 0 : at + kStage;
+            }
             }
             // store the group's rows (and their mirror images below the diagonal in a symmetric class)
             typedef int32_t intx4 __attribute__((ext_vector_type(4)));
@@ -832,7 +844,7 @@ template <bool WD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_class_f64(ProblemDesc64 pd) {
     extern __shared__ __align__(16) char smem[];
-    const F64Lds lds = f64_lds(smem, pd.max_terms);
+    const F64Lds lds = f64_lds(smem, pd.max_terms, pd.tile_rows);
     const int item = blockIdx.x;        // pd.mtiles: a dispatch table, slot per workgroup
     const int groups = pd.mtiles[4 * item + 2];
     if (groups == 0) return;            // an empty slot
@@ -882,7 +894,7 @@ void k_batch_f64(const ProblemDesc64 *__restrict__ probs, const int32_t *__restr
                  int32_t parts) {
     extern __shared__ __align__(16) char smem[];
     __shared__ int32_t sItem;
-    const F64Lds lds = f64_lds(smem, max_terms);
+    const F64Lds lds = f64_lds(smem, max_terms, 64);
     const int home = blockIdx.x % nq;
     int tried = 0;                       // queues found empty (thread 0)
     for (;;) {
@@ -1813,7 +1825,7 @@ hipError_t launch_expand(const double *u64, const int32_t *items, int64_t nitems
 // other's limit.
 static hipError_t f64_allow_lds(const void *kernel, int bytes) {
     if (bytes <= 64 * 1024) return hipSuccess;
-    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, f64_lds_bytes(kMaxClassTerms));
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, f64_lds_bytes(kMaxClassTerms, 64));
 }
 
 // A short launch splits each tile's row groups over up to eight workgroups, to
@@ -1839,8 +1851,8 @@ hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st) {
     if (a.nblocks == 0) return hipSuccess;
     if (prec == 0) {
         ProblemDesc64 pd{a.mtiles, a.classes, a.class_terms, a.class_blk, a.class_itab, a.u64t, a.ninv, a.out,
-                         a.du64, a.blk_uid, a.outD, a.masks.units, a.masks.cols, a.masks.overflow, a.max_terms};
-        const int lds = f64_lds_bytes(a.max_terms);
+                         a.du64, a.blk_uid, a.outD, a.masks.units, a.masks.cols, a.masks.overflow, a.max_terms, a.tile_rows};
+        const int lds = f64_lds_bytes(a.max_terms, a.tile_rows);
         const void *k = a.outD ? (const void *)k_class_f64<true> : (const void *)k_class_f64<false>;
         const hipError_t e = f64_allow_lds(k, lds);
         if (e != hipSuccess) return e;
@@ -1879,7 +1891,7 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t st) {
     if (b.prec == 0) {                   // FP64: N^-1 is read as given
         if (b.persistent) {
             if (b.nitems > 0)
-                hipLaunchKernelGGL(k_batch_f64, dim3((unsigned)b.nworkgroups), dim3(256), f64_lds_bytes(b.max_terms), st,
+                hipLaunchKernelGGL(k_batch_f64, dim3((unsigned)b.nworkgroups), dim3(256), f64_lds_bytes(b.max_terms, 64), st,
                                    b.desc64, b.items, b.qb, b.nq, b.counters, b.max_terms, (int32_t)f64_parts(b.nitems));
         } else {
             for (int p = 0; p < b.nprob; ++p) {
@@ -1887,7 +1899,7 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t st) {
                 ProblemDesc64 d = b.host_desc64[p];
                 d.mtiles = b.gtiles[p];
                 hipLaunchKernelGGL(k_class_f64<false>, dim3((unsigned)b.ngtiles[p], f64_parts(b.ngtiles[p])), dim3(256),
-                                   f64_lds_bytes(d.max_terms), st, d);
+                                   f64_lds_bytes(d.max_terms, d.tile_rows), st, d);
             }
         }
         return hipGetLastError();
@@ -1935,7 +1947,7 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t st) {
 
 hipError_t batch_prepare(int prec, int max_terms, int *workgroups_per_cu) {
     if (prec == 0) {
-        const int lds = f64_lds_bytes(max_terms);
+        const int lds = f64_lds_bytes(max_terms, 64);
         hipError_t e = f64_allow_lds((const void *)k_batch_f64, lds);
         if (e == hipSuccess) e = f64_allow_lds((const void *)k_class_f64<false>, lds);
         if (e != hipSuccess) return e;
