@@ -1832,10 +1832,17 @@ static hipError_t f64_allow_lds(const void *kernel, int bytes) {
 // have two per CU (each repeats the tile's tables).  Measured, D-hat and
 // contraction, one / two / four / eight parts: 57 tiles (lmax 64) 518 / 322 /
 // 236 / 178 us, 208 (128) 460 / 308 / 265, 350 (256) 879 / 557 / 547, 987 (512)
-// 1270 / 1278 / 1321, 8848 (2048) 13373 / 13562 / 13916.
-static unsigned f64_parts(int64_t tiles) {
+// 1270 / 1278 / 1321, 8848 (2048) 13373 / 13562 / 13916.  Where a class has many
+// terms (two grids) its tiles are long and unlike, a part's share of the tables
+// is small, and the launch's end costs more: 1072 tiles of up to 36 terms (lmax
+// 256 with 512, beam 5 pixels) one / two / four parts 3301 / 3119 / 3039 us, 320
+// of up to 42 (60 with 120) four / eight 1441 / 1194 (whole tiles of the full
+// contraction: 1293), 564 of up to 16 (256 with
+// 307) two / four / eight 1246 / 1126 / 1164.
+static unsigned f64_parts(int64_t tiles, int terms) {
+    const int64_t enough = terms > 12 ? 128 * terms : 1024;
     unsigned parts = 1;
-    while (parts < 8 && tiles * parts < 1024) parts *= 2;
+    while (parts < 8 && tiles * parts < enough) parts *= 2;
     return parts;
 }
 
@@ -1856,7 +1863,7 @@ hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st) {
         const void *k = a.outD ? (const void *)k_class_f64<true> : (const void *)k_class_f64<false>;
         const hipError_t e = f64_allow_lds(k, lds);
         if (e != hipSuccess) return e;
-        const dim3 grid((unsigned)a.nmtiles, f64_parts(a.nmtiles));
+        const dim3 grid((unsigned)a.nmtiles, f64_parts(a.nmtiles, a.max_terms));
         if (a.outD) hipLaunchKernelGGL(k_class_f64<true>, grid, dim3(256), lds, st, pd);
         else hipLaunchKernelGGL(k_class_f64<false>, grid, dim3(256), lds, st, pd);
         return hipGetLastError();
@@ -1892,13 +1899,13 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t st) {
         if (b.persistent) {
             if (b.nitems > 0)
                 hipLaunchKernelGGL(k_batch_f64, dim3((unsigned)b.nworkgroups), dim3(256), f64_lds_bytes(b.max_terms, 64), st,
-                                   b.desc64, b.items, b.qb, b.nq, b.counters, b.max_terms, (int32_t)f64_parts(b.nitems));
+                                   b.desc64, b.items, b.qb, b.nq, b.counters, b.max_terms, (int32_t)f64_parts(b.nitems, b.max_terms));
         } else {
             for (int p = 0; p < b.nprob; ++p) {
                 if (b.ngtiles[p] == 0) continue;
                 ProblemDesc64 d = b.host_desc64[p];
                 d.mtiles = b.gtiles[p];
-                hipLaunchKernelGGL(k_class_f64<false>, dim3((unsigned)b.ngtiles[p], f64_parts(b.ngtiles[p])), dim3(256),
+                hipLaunchKernelGGL(k_class_f64<false>, dim3((unsigned)b.ngtiles[p], f64_parts(b.ngtiles[p], b.max_terms)), dim3(256),
                                    f64_lds_bytes(d.max_terms, d.tile_rows), st, d);
             }
         }
