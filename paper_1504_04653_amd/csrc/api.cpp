@@ -447,6 +447,7 @@ sympix_status sample_btnb(const sympix_grid *g, const sympix_kernel *d, const sy
     a.u64t = b->u64t;
     a.ut32 = b->ut32;
     a.masks = b->masks;
+    a.cut = b->cut_spacings > 0 ? 1 : 0;
     a.skip = sympix::short_cut(prec, b->cut_spacings) ? 1 : 0;
     if (pat) {
         const DevClasses *dc = nullptr;
@@ -1134,7 +1135,8 @@ sympix_status sympix_batch_create(const sympix_problem *p, int32_t n, int32_t pr
             const std::vector<int32_t> &tiles = t == SYMPIX_TILES_64 ? geo.cls.mtiles : geo.cls.mtiles32;
             sympix::ProblemDesc64 d64{dtiles, dg->classes, dg->class_terms, dg->class_blk, dg->class_itab,
                                       p[i].b->u64t, p[i].ninv_dev, p[i].out_dev, nullptr, nullptr, nullptr,
-                                      p[i].b->masks.units, p[i].b->masks.cols, p[i].b->masks.overflow, bt->max_terms, 64};
+                                      p[i].b->masks.units, p[i].b->masks.cols, p[i].b->masks.overflow, bt->max_terms, 64,
+                                      p[i].b->cut_spacings > 0 ? 1 : 0};
             bt->hdesc64[t].push_back(d64);
             sympix::ProblemDesc d{dtiles, dg->classes, dg->class_terms, dg->class_blk, dg->class_itab,
                                   p[i].b->ut32, nullptr, p[i].out_dev, nullptr, nullptr, nullptr,
@@ -1563,6 +1565,7 @@ sympix_status sympix_sample_BtNB_cross(const sympix_cross *c, const sympix_kerne
     a.u64t = b->u64t;
     a.ut32 = b->ut32;
     a.masks = b->masks;
+    a.cut = b->cut_spacings > 0 ? 1 : 0;
     a.skip = sympix::short_cut(prec, b->cut_spacings) ? 1 : 0;
     a.classes = dx->classes;
     a.class_terms = dx->class_terms;

@@ -87,7 +87,8 @@ struct BtnbArgs {
     UnitMasks masks;          // of the unique blocks u64t / ut32
     int32_t max_terms;        // most terms of a class
     int32_t tile_rows;        // most members of a tile of mtiles: 64 or 32 (FP64 alone)
-    int32_t skip;             // the kernel's cut is a short_cut in this precision
+    int32_t cut;              // the kernel has a radial cut
+    int32_t skip;             // it is a short_cut in this precision
     // optional D-hat blocks written by the same launch:
     // stored block n gets unique block blk_uid[n] of du64 (row-major FP64)
     const double *du64;
@@ -122,6 +123,7 @@ struct ProblemDesc64 {
     const int32_t *overflow;
     int32_t max_terms;        // most terms a class of the launch has
     int32_t tile_rows;        // most members a tile of the launch has: 64 or 32
+    int32_t cut;              // the kernel has a radial cut
 };
 
 // Operands of the split-BF16 class GEMM (device pointers).

@@ -540,24 +540,30 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
         if constexpr (WD) lds.blk[64 + lane] = blk >= 0 ? pd.blk_uid[blk] : 0;   // D-hat source block
     }
     for (int x = tid; x < 2 * nterms; x += 256) lds.term[x] = terms[x];
-    for (int x = tid; x < 32 * nterms; x += 256)                           // 64 masks of 2 bytes per term
-        ((uint32_t *)lds.mask)[x] = ((const uint32_t *)pd.units)[(int64_t)terms[2 * (x >> 5)] * 32 + (x & 31)];
-    for (int x = tid; x < 4 * nterms; x += 256)
-        lds.cols[x] = pd.unit_cols[(int64_t)terms[2 * (x >> 2) + 1] * 4 + (x & 3)];
-    __syncthreads();
-    bool bad = *pd.overflow != 0;        // sixteen threads per (member row, term), four pixels each
-    for (int r = tid >> 4; r < 16 * NI; r += 16)
-        for (int e = 0; e < nterms; e += 4) {        // four loads in flight
-            doublex4 v[4];
+    // A kernel without a cut has no zeros worth a look: every step runs in full,
+    // and nothing is asked of N^-1 (lmax 256 with 512: 3363 -> 3287 us)
+    bool all = pd.cut == 0;
+    if (!all) {
+        for (int x = tid; x < 32 * nterms; x += 256)                       // 64 masks of 2 bytes per term
+            ((uint32_t *)lds.mask)[x] = ((const uint32_t *)pd.units)[(int64_t)terms[2 * (x >> 5)] * 32 + (x & 31)];
+        for (int x = tid; x < 4 * nterms; x += 256)
+            lds.cols[x] = pd.unit_cols[(int64_t)terms[2 * (x >> 2) + 1] * 4 + (x & 3)];
+        __syncthreads();
+        bool bad = *pd.overflow != 0;    // sixteen threads per (member row, term), four pixels each
+        for (int r = tid >> 4; r < 16 * NI; r += 16)
+            for (int e = 0; e < nterms; e += 4) {    // four loads in flight
+                doublex4 v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                v[i] = *(const doublex4 *)(wv + (int64_t)lds.tile[r * lds.stride + min(e + i, nterms - 1)] * 64 + 4 * lr);
+                for (int i = 0; i < 4; ++i)
+                    v[i] = *(const doublex4 *)(wv + (int64_t)lds.tile[r * lds.stride + min(e + i, nterms - 1)] * 64 + 4 * lr);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) bad |= not_finite(v[i][t]);
-        }
-    if (__syncthreads_or(bad)) {
+                    for (int t = 0; t < 4; ++t) bad |= not_finite(v[i][t]);
+            }
+        all = __syncthreads_or(bad) != 0;
+    }
+    if (all) {
         for (int x = tid; x < 32 * nterms; x += 256) ((uint32_t *)lds.mask)[x] = 0xffffffffu;
         for (int x = tid; x < 2 * nterms; x += 256) ((uint32_t *)lds.cols)[x] = 0xffffffffu;
         __syncthreads();
@@ -1836,9 +1842,9 @@ static hipError_t f64_allow_lds(const void *kernel, int bytes) {
 // terms (two grids) its tiles are long and unlike, a part's share of the tables
 // is small, and the launch's end costs more: 1072 tiles of up to 36 terms (lmax
 // 256 with 512, beam 5 pixels) one / two / four parts 3301 / 3119 / 3039 us, 320
-// of up to 42 (60 with 120) four / eight 1441 / 1194 (whole tiles of the full
-// contraction: 1293), 564 of up to 16 (256 with
-// 307) two / four / eight 1246 / 1126 / 1164.
+// of up to 42 (60 with 120) four / eight 1441 / 1194 (the full contraction on
+// whole tiles: 1293), 564 of up to 16 (256 with 307) two / four / eight 1246 /
+// 1126 / 1164.
 static unsigned f64_parts(int64_t tiles, int terms) {
     const int64_t enough = terms > 12 ? 128 * terms : 1024;
     unsigned parts = 1;
@@ -1858,7 +1864,7 @@ hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st) {
     if (a.nblocks == 0) return hipSuccess;
     if (prec == 0) {
         ProblemDesc64 pd{a.mtiles, a.classes, a.class_terms, a.class_blk, a.class_itab, a.u64t, a.ninv, a.out,
-                         a.du64, a.blk_uid, a.outD, a.masks.units, a.masks.cols, a.masks.overflow, a.max_terms, a.tile_rows};
+                         a.du64, a.blk_uid, a.outD, a.masks.units, a.masks.cols, a.masks.overflow, a.max_terms, a.tile_rows, a.cut};
         const int lds = f64_lds_bytes(a.max_terms, a.tile_rows);
         const void *k = a.outD ? (const void *)k_class_f64<true> : (const void *)k_class_f64<false>;
         const hipError_t e = f64_allow_lds(k, lds);
