@@ -368,16 +368,28 @@ __device__ __forceinline__ void dcopy_store(const DCopy<N> &dc, int lane) {
         if (dc.dst[r]) __builtin_nontemporal_store(dc.v[r], (doublex2 *)(dc.dst[r] + 2 * lane));
 }
 
+// The thread's index.  Where a kernel loops over work items (BATCH) it is opaque to
+// the compiler: what a tile's body derives from it (swizzles, staging offsets, of
+// every tile height and form) would otherwise be computed once ahead of the loop
+// and held in registers through all bodies, which spilled (104 bytes per lane in
+// FP64, 256 in BF16x6).
+template <bool BATCH>
+__device__ __forceinline__ int thread_index() {
+    int t = threadIdx.x;
+    if constexpr (BATCH) asm volatile("" : "+v"(t));
+    return t;
+}
+
 // A class without contraction terms: between two grids, when the auxiliary
 // grid is the coarser one, a stored block (J, K) can have no tile I that
 // neighbours both J and K, so the sum of Eq. 15 is empty and the block is
 // zero.  The workgroup clears the member tile's blocks (and gives them their
 // D-hat copies), without LDS; the caller returns right after.
 template <int NT, bool WD, class PD>
-__device__ __forceinline__ void empty_class_tile(const PD &pd, const DevClass &cl, int m0, int rows, int tid) {
+__device__ __forceinline__ void empty_class_tile(const PD &pd, const DevClass &cl, int m0, int rows) {
     constexpr int kChunks = kBlockElems / 2;            // 16-byte chunks of a block
     const int nm = min(rows, cl.nblocks - m0);
-    for (int c = tid; c < nm * kChunks; c += NT) {
+    for (int c = threadIdx.x; c < nm * kChunks; c += NT) {
         const int m = c / kChunks, q = c - m * kChunks;
         const int64_t blk = pd.cblk[cl.blk0 + m0 + m];
         __builtin_nontemporal_store(doublex2{0.0, 0.0}, (doublex2 *)(pd.out + blk * kBlockElems) + q);
@@ -509,14 +521,15 @@ __device__ __forceinline__ bool not_finite(double v) {
     return ((uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32) & 0x7ff00000u) == 0x7ff00000u;
 }
 
-template <int NI, bool WD>
-__device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item, int part, int parts, int tid, const F64Lds &lds) {
+template <int NI, bool WD, bool BATCH>
+__device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item, int part, int parts, const F64Lds &lds) {
     constexpr int R = f64_rows(NI);
     constexpr int kWRows = NI == 4 ? 64 : 32;    // rows of W staged
     constexpr int kStageU2 = kWRows * 128, kStageU1 = kStageU2 + 64 * 128, kStage = f64_stage_bytes(kWRows);
     const double *__restrict__ ut = pd.u64t;
     const double *__restrict__ wv = pd.w;
     double *__restrict__ out = pd.out;
+    const int tid = thread_index<BATCH>();
     const int cls = pd.mtiles[4 * item], m0 = pd.mtiles[4 * item + 1];
     const DevClass cl = pd.classes[cls];
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -524,7 +537,7 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
     const int nterms = __builtin_amdgcn_readfirstlane(cl.nterms);
     const int32_t *terms = pd.cterms + 2 * cl.term0;
     if (nterms == 0) {
-        if (part == 0) empty_class_tile<256, WD>(pd, cl, m0, 16 * NI, tid);
+        if (part == 0) empty_class_tile<256, WD>(pd, cl, m0, 16 * NI);
         return;
     }
 
@@ -854,9 +867,9 @@ void k_class_f64(ProblemDesc64 pd) {
     const int item = blockIdx.x;        // pd.mtiles: a dispatch table, slot per workgroup
     const int groups = pd.mtiles[4 * item + 2];
     if (groups == 0) return;            // an empty slot
-    if (groups == 4) class_f64_tile<4, WD>(pd, item, blockIdx.y, gridDim.y, threadIdx.x, lds);
-    else if (groups == 2) class_f64_tile<2, WD>(pd, item, blockIdx.y, gridDim.y, threadIdx.x, lds);
-    else class_f64_tile<1, WD>(pd, item, blockIdx.y, gridDim.y, threadIdx.x, lds);
+    if (groups == 4) class_f64_tile<4, WD, false>(pd, item, blockIdx.y, gridDim.y, lds);
+    else if (groups == 2) class_f64_tile<2, WD, false>(pd, item, blockIdx.y, gridDim.y, lds);
+    else class_f64_tile<1, WD, false>(pd, item, blockIdx.y, gridDim.y, lds);
 }
 
 // Queue draining shared by the persistent batch kernels: thread 0 takes the
@@ -876,19 +889,6 @@ __device__ __forceinline__ int batch_next_item(const int32_t *__restrict__ qb, i
         ++tried;
     }
     return it;
-}
-
-// The thread's index where a kernel loops over work items, opaque to the
-// compiler: what a tile's body derives from it (swizzles, staging offsets, of
-// every tile height and form) would otherwise be computed once ahead of the
-// loop and held in registers through all bodies, which spilled (104 to 256
-// bytes per lane).  Four levels from lmax 512 down, without / with it: BF16x6
-// at beams of 2.5 pixels 1542 / 1506 us, at 5 pixels 1694 / 1620; BF16x3 1132 /
-// 1100 and 1160 / 1115; FP64 at 5 pixels 3523 / 3496.
-__device__ __forceinline__ int thread_index() {
-    int t = threadIdx.x;
-    asm volatile("" : "+v"(t));
-    return t;
 }
 
 // a10 in FP64: the FP64 class GEMM of many problems in one persistent launch
@@ -912,10 +912,10 @@ void k_batch_f64(const ProblemDesc64 *__restrict__ probs, const int32_t *__restr
         const int at = it / parts, part = it % parts;
         const ProblemDesc64 pd = probs[items[2 * at]];
         const int item = items[2 * at + 1];
-        const int groups = pd.mtiles[4 * item + 2], tid = thread_index();
-        if (groups == 4) class_f64_tile<4, false>(pd, item, part, parts, tid, lds);
-        else if (groups == 2) class_f64_tile<2, false>(pd, item, part, parts, tid, lds);
-        else class_f64_tile<1, false>(pd, item, part, parts, tid, lds);
+        const int groups = pd.mtiles[4 * item + 2];
+        if (groups == 4) class_f64_tile<4, false, true>(pd, item, part, parts, lds);
+        else if (groups == 2) class_f64_tile<2, false, true>(pd, item, part, parts, lds);
+        else class_f64_tile<1, false, true>(pd, item, part, parts, lds);
     }
 }
 
@@ -953,9 +953,9 @@ struct SkipLds {
 // the row quads of this part of the tile are listed.  Returns the length of the
 // list.
 template <int NI, class PD, class Finite>
-__device__ __forceinline__ int build_skip(const PD &pd, int nterms, int part, int parts, int tid, const int32_t *sTerm, SkipLds &sk,
+__device__ __forceinline__ int build_skip(const PD &pd, int nterms, int part, int parts, const int32_t *sTerm, SkipLds &sk,
                                           const Finite &w_finite) {
-    const int lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63;
     for (int x = tid; x < 32 * nterms; x += 512)
         ((uint32_t *)sk.mask)[x] = ((const uint32_t *)pd.units)[(int64_t)sTerm[2 * (x >> 5)] * 32 + (x & 31)];
     for (int x = tid; x < 4 * nterms; x += 512) sk.cols[x] = pd.unit_cols[(int64_t)sTerm[2 * (x >> 2) + 1] * 4 + (x & 3)];
@@ -1010,12 +1010,13 @@ __global__ __launch_bounds__(256) void k_ninv_f32(const double *__restrict__ nin
 // One member tile (item) of one problem with NI groups of 16 member rows; all
 // 512 threads of the workgroup take part.  sTile / sBlk / sTerm are the
 // workgroup's LDS tables, sW / sU its four staging buffers.
-template <int NI, bool WD, bool SKIP>
-__device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, int part, int parts, int tid, int32_t *sTile,
-                                               int32_t *sBlk, int32_t *sTerm, floatx4 *sW, floatx4 *sU, SkipLds &sk) {
+template <int NI, bool WD, bool SKIP, bool BATCH>
+__device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, int part, int parts, int32_t *sTile,
+                                               int32_t *sBlk, int32_t *sTerm, floatx4 *sW, floatx4 *sU, SkipLds *sk) {
     const float *__restrict__ ut32 = pd.ut32;
     double *__restrict__ out = pd.out;
     constexpr int NW = 8, NT = 64 * NW, RP = NW / 2, RPW = 64 / RP;
+    const int tid = thread_index<BATCH>();
     const int cls = pd.mtiles[4 * item], m0 = pd.mtiles[4 * item + 1];
     const DevClass cl = pd.classes[cls];
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1024,7 +1025,7 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     const int nterms = cl.nterms;
     const int32_t *terms = pd.cterms + 2 * cl.term0;
     if (nterms == 0) {
-        if (part == 0) empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI, tid);
+        if (part == 0) empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI);
         return;
     }
 
@@ -1043,7 +1044,7 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     // SKIP false: every term of every row, in order
     const int quad0 = 16 * part / parts;
     int total = (16 * (part + 1) / parts - quad0) * nterms;
-    if constexpr (SKIP) total = build_skip<NI>(pd, nterms, part, parts, tid, sTerm, sk, [&](int r, int e, int c) {
+    if constexpr (SKIP) total = build_skip<NI>(pd, nterms, part, parts, sTerm, *sk, [&](int r, int e, int c) {
         const floatx4 v = *(const floatx4 *)(pd.wf + (int64_t)sTile[r * kTileStride + e] * 64 + 4 * c);
         return fabsf(v[0]) < INFINITY && fabsf(v[1]) < INFINITY && fabsf(v[2]) < INFINITY && fabsf(v[3]) < INFINITY;
     });
@@ -1122,7 +1123,7 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
         for (int jj = 0; jj < 2; ++jj) {
             // bit g: ring g of this half's four columns can be nonzero
             const uint32_t rings = (jj ? on1 : on0) >> (8 * h) & 255u;
-            if ((SKIP || S) && rings == 0) continue;
+            if (SKIP ? rings == 0 : S && jj >= ng) continue;   // symmetric class: this wave's groups of the row
             const int b = S ? 16 * (jj ? g1 : g0) + lr : 32 * ch + 16 * jj + lr;
             float m[8];
 #pragma unroll
@@ -1154,7 +1155,7 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     // entry it of the list (past its end the last one), and this wave's MFMAs of
     // an entry, read one iteration ahead: bit 8 h + g of a column group
     auto entry = [&](int it, int before) {   // before: entry it - 1
-        if constexpr (SKIP) return (int)sk.list[min(it, total - 1)];
+        if constexpr (SKIP) return (int)sk->list[min(it, total - 1)];
         else if (it == 0) return 256 * quad0;
         else if (it >= total) return before;
         else return (before & 255) + 1 < nterms ? before + 1 : (before | 255) + 1;
@@ -1172,13 +1173,10 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
         return q;
     };
     auto on_of = [&](int c, const Groups &q, uint32_t &o0, uint32_t &o1) {
-        if constexpr (!SKIP) {
-            o0 = q.ng > 0 ? 0xffffu : 0u;
-            o1 = q.ng > 1 ? 0xffffu : 0u;
-        } else {
-            const uint32_t m = sk.mask[64 * (c & 255) + rw + RP * (c >> 8)];
-            o0 = q.ng > 0 ? m & sk.cols[4 * (c & 255) + q.g0] : 0u;
-            o1 = q.ng > 1 ? m & sk.cols[4 * (c & 255) + q.g1] : 0u;
+        if constexpr (SKIP) {
+            const uint32_t m = sk->mask[64 * (c & 255) + rw + RP * (c >> 8)];
+            o0 = q.ng > 0 ? m & sk->cols[4 * (c & 255) + q.g0] : 0u;
+            o1 = q.ng > 1 ? m & sk->cols[4 * (c & 255) + q.g1] : 0u;
         }
     };
     Stage s0, s1;
@@ -1208,7 +1206,7 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     auto rows = [&](auto symt) {
         constexpr bool S = decltype(symt)::value;
         Groups gr = groups_of(symt, c0 >> 8);
-        uint32_t on0, on1;
+        uint32_t on0 = 0, on1 = 0;           // (SKIP)
         on_of(c0, gr, on0, on1);
         on0 = uniform(on0);
         on1 = uniform(on1);
@@ -1218,7 +1216,7 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
             const int a = rw + RP * x, a1 = rw + RP * x1;
             const int ng = gr.ng, g0 = gr.g0, g1 = gr.g1;
             const Groups gn = groups_of(symt, x1);
-            uint32_t raw_on0, raw_on1;
+            uint32_t raw_on0 = 0, raw_on1 = 0;
             on_of(c1, gn, raw_on0, raw_on1);
             if constexpr (SKIP) {
 #pragma unroll
@@ -1235,7 +1233,7 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
             for (int i = 0; i < NI; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
-                    if ((!SKIP && !S) || (j ? on1 : on0) != 0) {
+                    if (SKIP ? (j ? on1 : on0) != 0 : !S || j < ng) {
 #pragma unroll
                         for (int v = 0; v < 4; ++v) acc[i][j][v] += (double)psum[i][j][v];
                     }
@@ -1280,19 +1278,14 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
     }
 }
 
-template <bool WD>
-__device__ __forceinline__ void class_f32_item(const ProblemDesc &pd, int item, int part, int parts, int tid, int32_t *sTile, int32_t *sBlk,
-                                               int32_t *sTerm, floatx4 *sW, floatx4 *sU, SkipLds &sk) {
+template <bool WD, bool SKIP, bool BATCH>
+__device__ __forceinline__ void class_f32_item(const ProblemDesc &pd, int item, int part, int parts, int32_t *sTile, int32_t *sBlk,
+                                               int32_t *sTerm, floatx4 *sW, floatx4 *sU, SkipLds *sk) {
     const int groups = pd.mtiles[4 * item + 2];
     if (groups == 0) return;            // an empty slot of a dispatch table
-    auto tile = [&](auto skip) {
-        constexpr bool SKIP = decltype(skip)::value;
-        if (groups == 4) class_f32_tile<4, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
-        else if (groups == 2) class_f32_tile<2, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
-        else class_f32_tile<1, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
-    };
-    if (pd.skip != 0) tile(std::true_type());
-    else tile(std::false_type());
+    if (groups == 4) class_f32_tile<4, WD, SKIP, BATCH>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+    else if (groups == 2) class_f32_tile<2, WD, SKIP, BATCH>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+    else class_f32_tile<1, WD, SKIP, BATCH>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
 }
 
 template <bool WD>
@@ -1304,7 +1297,8 @@ void k_class_f32(ProblemDesc pd) {
     __shared__ floatx4 sW[4 * 512];                  // staged W, four buffers
     __shared__ floatx4 sU[4 * 512];                  // staged B_IK values, four buffers
     __shared__ SkipLds sk;
-    class_f32_item<WD>(pd, blockIdx.x, blockIdx.y, gridDim.y, threadIdx.x, sTile, sBlk, sTerm, sW, sU, sk);
+    if (pd.skip != 0) class_f32_item<WD, true, false>(pd, blockIdx.x, blockIdx.y, gridDim.y, sTile, sBlk, sTerm, sW, sU, &sk);
+    else class_f32_item<WD, false, false>(pd, blockIdx.x, blockIdx.y, gridDim.y, sTile, sBlk, sTerm, sW, sU, &sk);
 }
 
 // ---------------------------------------------------------------------------
@@ -1339,7 +1333,8 @@ void k_batch_f32(const ProblemDesc *__restrict__ probs, const int32_t *__restric
         if (it < 0) break;
         const int at = it / parts;
         const ProblemDesc pd = probs[items[2 * at]];
-        class_f32_item<false>(pd, items[2 * at + 1], it % parts, parts, thread_index(), sTile, sBlk, sTerm, sW, sU, sk);
+        if (pd.skip != 0) class_f32_item<false, true, true>(pd, items[2 * at + 1], it % parts, parts, sTile, sBlk, sTerm, sW, sU, &sk);
+        else class_f32_item<false, false, true>(pd, items[2 * at + 1], it % parts, parts, sTile, sBlk, sTerm, sW, sU, &sk);
     }
 }
 
@@ -1394,8 +1389,6 @@ __global__ __launch_bounds__(256) void k_split_ninv(const double *__restrict__ n
     w2[i] = bf16_bits((float)(r1 - (double)bf16_value(m)));
 }
 
-// Of three values by value: an index into the descriptor's array would keep the
-// descriptor of a batch problem in scratch memory.
 __device__ __forceinline__ const uint16_t *one_of(int k, const uint16_t *a, const uint16_t *b, const uint16_t *c) {
     return k == 0 ? a : k == 1 ? b : c;
 }
@@ -1419,13 +1412,14 @@ __device__ __forceinline__ const uint16_t *one_of(int k, const uint16_t *a, cons
 // and step (loaded with one step's loads, stored after the next step's), so
 // that these writes proceed under the contraction's arithmetic; chunks left
 // after the last step are copied at the end of the tile.
-template <int NP, int NI, bool WD, bool SKIP>
-__device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item, int part, int parts, int tid, int32_t *sTile,
+template <int NP, int NI, bool WD, bool SKIP, bool BATCH>
+__device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item, int part, int parts, int32_t *sTile,
                                                 int32_t *sBlk, int32_t *sTerm, u16x8 *sW, floatx4 *sU, SkipLds &sk) {
     const float *__restrict__ ut32 = pd.ut32;
     double *__restrict__ out = pd.out;
     const int cls = pd.mtiles[4 * item], m0 = pd.mtiles[4 * item + 1];
     const DevClass cl = pd.classes[cls];
+    const int tid = thread_index<BATCH>();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int NW = 8, NT = 64 * NW;              // waves, threads
     constexpr int RP = NW / 2, RPW = 64 / RP;          // row phases, rows per wave
@@ -1434,7 +1428,7 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     const int nterms = cl.nterms;
     const int32_t *terms = pd.cterms + 2 * cl.term0;
     if (nterms == 0) {
-        if (part == 0) empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI, tid);
+        if (part == 0) empty_class_tile<NT, WD>(pd, cl, m0, 16 * NI);
         return;
     }
 
@@ -1453,7 +1447,7 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     // SKIP false: every term of every row, in order
     const int quad0 = 16 * part / parts;
     int total = (16 * (part + 1) / parts - quad0) * nterms;
-    if constexpr (SKIP) total = build_skip<NI>(pd, nterms, part, parts, tid, sTerm, sk, [&](int r, int e, int c) {
+    if constexpr (SKIP) total = build_skip<NI>(pd, nterms, part, parts, sTerm, sk, [&](int r, int e, int c) {
         // the leading parts: exponents of two BF16 values per word, all ones if not finite
         const uint64_t v = *(const uint64_t *)(pd.w[0] + (int64_t)sTile[r * kTileStride + e] * 64 + 4 * c);
         uint64_t inf = 0;
@@ -1478,7 +1472,9 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
         int c = tid + NT * r;
         if (c >= 256 * NP) c -= 256;
         const int k = __builtin_amdgcn_readfirstlane(c >> 8), q = c & 255, row = q >> 2, sub = q & 3;
-        wsrc[r] = one_of(k, pd.w[0], pd.w[1], pd.w[2]) + 8 * sub;
+        // (an index into a copied descriptor's array would keep it in scratch memory)
+        if constexpr (BATCH) wsrc[r] = one_of(k, pd.w[0], pd.w[1], pd.w[2]) + 8 * sub;
+        else wsrc[r] = pd.w[k] + 8 * sub;
         wrow[r] = min(row, 16 * NI - 1) * kTileStride;
         // LDS layouts, in 16-byte chunks: W row r (64 bytes) keeps its chunk c at
         // 4 r + (c ^ wsw(r)), a B_IK row b (128 bytes) its chunk c at 8 b + (c ^
@@ -1711,19 +1707,23 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
 }
 
 // One member tile (item) of one problem; sTile, sBlk, sTerm, sW and sU are the
-// workgroup's LDS tables and staging buffers.
-template <int NP, bool WD>
-__device__ __forceinline__ void class_bf16_item(const ProblemDescB &pd, int item, int part, int parts, int tid, int32_t *sTile, int32_t *sBlk,
+// workgroup's LDS tables and staging buffers.  FORM kFull or kSkip: the form of
+// every problem of the launch; kEither: each problem's own.
+enum Form { kFull, kSkip, kEither };
+
+template <int NP, bool WD, int FORM = kEither, bool BATCH = false>
+__device__ __forceinline__ void class_bf16_item(const ProblemDescB &pd, int item, int part, int parts, int32_t *sTile, int32_t *sBlk,
                                                 int32_t *sTerm, u16x8 *sW, floatx4 *sU, SkipLds &sk) {
     const int groups = pd.mtiles[4 * item + 2];
     if (groups == 0) return;            // an empty slot of a dispatch table
     auto tile = [&](auto skip) {
         constexpr bool SKIP = decltype(skip)::value;
-        if (groups == 4) class_bf16_tile<NP, 4, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
-        else if (groups == 2) class_bf16_tile<NP, 2, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
-        else class_bf16_tile<NP, 1, WD, SKIP>(pd, item, part, parts, tid, sTile, sBlk, sTerm, sW, sU, sk);
+        if (groups == 4) class_bf16_tile<NP, 4, WD, SKIP, BATCH>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+        else if (groups == 2) class_bf16_tile<NP, 2, WD, SKIP, BATCH>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
+        else class_bf16_tile<NP, 1, WD, SKIP, BATCH>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
     };
-    if (pd.skip != 0) tile(std::true_type());
+    if constexpr (FORM != kEither) tile(std::bool_constant<FORM == kSkip>());
+    else if (pd.skip != 0) tile(std::true_type());
     else tile(std::false_type());
 }
 
@@ -1736,12 +1736,19 @@ void k_class_bf16(ProblemDescB pd) {
     __shared__ u16x8 sW[4 * NP * 64 * 4];            // staged W, four buffers
     __shared__ floatx4 sU[4 * 512];                  // staged B_IK values, four buffers
     __shared__ SkipLds sk;
-    class_bf16_item<NP, WD>(pd, blockIdx.x, blockIdx.y, gridDim.y, threadIdx.x, sTile, sBlk, sTerm, sW, sU, sk);
+    class_bf16_item<NP, WD>(pd, blockIdx.x, blockIdx.y, gridDim.y, sTile, sBlk, sTerm, sW, sU, sk);
 }
 
 // Many problems in one persistent launch, split BF16 (the queues and their
-// draining as in k_batch_f32; one 8-wave workgroup per CU).
-template <int NP>
+// draining as in k_batch_f32; one 8-wave workgroup per CU).  A kernel per form,
+// with bodies of its own (thread_index), and one for batches of both, which runs
+// the bodies of the single launches: with the thread's index opaque in those too
+// BF16x6 alone took 446 us at lmax 300 (437 before), and a batch of both forms
+// gains nothing by it.  That kernel spills 100 bytes per lane in BF16x6.  Four
+// levels from lmax 512 down, one spilling kernel for all / this: BF16x6 at beams
+// of 2.5 pixels 1542 / 1519 us, at 3 (both forms) 1684 / 1616, at 5 1692 / 1657;
+// BF16x3 1133 / 1099, 1155 / 1124 and 1159 / 1124.
+template <int NP, int FORM>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_batch_bf16(const ProblemDescB *__restrict__ probs, const int32_t *__restrict__ items,
                   const int32_t *__restrict__ qb, int32_t nq, int32_t *__restrict__ counters, int32_t parts) {
@@ -1761,8 +1768,9 @@ void k_batch_bf16(const ProblemDescB *__restrict__ probs, const int32_t *__restr
         __syncthreads();                 // every thread has read sItem before it changes
         if (it < 0) break;
         const int at = it / parts;
-        const ProblemDescB pd = probs[items[2 * at]];
-        class_bf16_item<NP, false>(pd, items[2 * at + 1], it % parts, parts, thread_index(), sTile, sBlk, sTerm, sW, sU, sk);
+        using Desc = std::conditional_t<FORM != kEither, const ProblemDescB, const ProblemDescB &>;
+        Desc pd = probs[items[2 * at]];
+        class_bf16_item<NP, false, FORM, FORM != kEither>(pd, items[2 * at + 1], it % parts, parts, sTile, sBlk, sTerm, sW, sU, sk);
     }
 }
 
@@ -1860,6 +1868,12 @@ static unsigned tile_parts(int64_t tiles) {
     return parts;
 }
 
+// One launch of the FP32 class GEMM: with D-hat or without.
+static void run_class_f32(const ProblemDesc &d, dim3 grid, hipStream_t st) {
+    if (d.outD) hipLaunchKernelGGL(k_class_f32<true>, grid, dim3(512), 0, st, d);
+    else hipLaunchKernelGGL(k_class_f32<false>, grid, dim3(512), 0, st, d);
+}
+
 hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st) {
     if (a.nblocks == 0) return hipSuccess;
     if (prec == 0) {
@@ -1879,8 +1893,7 @@ hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st) {
                            a.npix, a.wf32);
         ProblemDesc pd{a.mtiles, a.classes, a.class_terms, a.class_blk, a.class_itab, a.ut32, a.wf32, a.out,
                        a.du64, a.blk_uid, a.outD, a.masks.units, a.masks.cols, a.masks.overflow, a.skip};
-        if (a.outD) hipLaunchKernelGGL(k_class_f32<true>, dim3((unsigned)a.nmtiles, tile_parts(a.nmtiles)), dim3(512), 0, st, pd);
-        else hipLaunchKernelGGL(k_class_f32<false>, dim3((unsigned)a.nmtiles, tile_parts(a.nmtiles)), dim3(512), 0, st, pd);
+        run_class_f32(pd, dim3((unsigned)a.nmtiles, tile_parts(a.nmtiles)), st);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_split_ninv, dim3((unsigned)((a.npix + 255) / 256)), dim3(256), 0, st, a.ninv,
@@ -1897,6 +1910,18 @@ hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st) {
         else hipLaunchKernelGGL((k_class_bf16<3, false>), grid, dim3(512), 0, st, pd);
     }
     return hipGetLastError();
+}
+
+template <int NP>
+static void run_batch_bf16(const BatchLaunch &b, dim3 grid, int32_t parts, hipStream_t st) {
+    int skips = 0;
+    for (int p = 0; p < b.nprob; ++p) skips += b.host_descb[p].skip != 0;
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(512), 0, st, b.descb, b.items, b.qb, b.nq, b.counters, parts);
+    };
+    if (skips == 0) run(k_batch_bf16<NP, kFull>);
+    else if (skips == b.nprob) run(k_batch_bf16<NP, kSkip>);
+    else run(k_batch_bf16<NP, kEither>);
 }
 
 hipError_t launch_batch(const BatchLaunch &b, hipStream_t st) {
@@ -1935,9 +1960,9 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t st) {
             if (!bf16)
                 hipLaunchKernelGGL(k_batch_f32, g, dim3(512), 0, st, b.desc, b.items, b.qb, b.nq, b.counters, parts);
             else if (b.prec == 2)
-                hipLaunchKernelGGL(k_batch_bf16<2>, g, dim3(512), 0, st, b.descb, b.items, b.qb, b.nq, b.counters, parts);
+                run_batch_bf16<2>(b, g, parts, st);
             else
-                hipLaunchKernelGGL(k_batch_bf16<3>, g, dim3(512), 0, st, b.descb, b.items, b.qb, b.nq, b.counters, parts);
+                run_batch_bf16<3>(b, g, parts, st);
         }
     } else {
         for (int p = 0; p < b.nprob; ++p) {
@@ -1946,7 +1971,7 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t st) {
             if (!bf16) {
                 ProblemDesc d = b.host_desc[p];
                 d.mtiles = b.gtiles[p];
-                hipLaunchKernelGGL(k_class_f32<false>, g, dim3(512), 0, st, d);
+                run_class_f32(d, g, st);
             } else {
                 ProblemDescB d = b.host_descb[p];
                 d.mtiles = b.gtiles[p];
@@ -1967,8 +1992,8 @@ hipError_t batch_prepare(int prec, int max_terms, int *workgroups_per_cu) {
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_f64, 256, lds);
     }
     if (prec == 1) return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_f32, 512, 0);
-    if (prec == 2) return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_bf16<2>, 512, 0);
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_bf16<3>, 512, 0);
+    if (prec == 2) return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_bf16<2, kEither>, 512, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_bf16<3, kEither>, 512, 0);
 }
 
 hipError_t launch_convolve(const double *u64, const int32_t *chunks, int64_t nchunks, const int32_t *slots,
