@@ -1288,7 +1288,9 @@ __device__ __forceinline__ void class_f32_item(const ProblemDesc &pd, int item, 
     else class_f32_tile<1, WD, SKIP, BATCH>(pd, item, part, parts, sTile, sBlk, sTerm, sW, sU, sk);
 }
 
-template <bool WD>
+// SKIP: products that the cut makes zero are left out (a kernel of its own: with
+// both forms in one, the full form at lmax 1500 took 7.04 ms, alone 6.93).
+template <bool WD, bool SKIP>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_class_f32(ProblemDesc pd) {
     __shared__ int32_t sTile[64 * kTileStride];   // tile I of (member row, term)
@@ -1296,9 +1298,12 @@ void k_class_f32(ProblemDesc pd) {
     __shared__ int32_t sTerm[2 * kMaxClassTerms];     // unique-block pairs of the class
     __shared__ floatx4 sW[4 * 512];                  // staged W, four buffers
     __shared__ floatx4 sU[4 * 512];                  // staged B_IK values, four buffers
-    __shared__ SkipLds sk;
-    if (pd.skip != 0) class_f32_item<WD, true, false>(pd, blockIdx.x, blockIdx.y, gridDim.y, sTile, sBlk, sTerm, sW, sU, &sk);
-    else class_f32_item<WD, false, false>(pd, blockIdx.x, blockIdx.y, gridDim.y, sTile, sBlk, sTerm, sW, sU, &sk);
+    SkipLds *sk = nullptr;
+    if constexpr (SKIP) {
+        __shared__ SkipLds lists;
+        sk = &lists;
+    }
+    class_f32_item<WD, SKIP, false>(pd, blockIdx.x, blockIdx.y, gridDim.y, sTile, sBlk, sTerm, sW, sU, sk);
 }
 
 // ---------------------------------------------------------------------------
@@ -1868,10 +1873,13 @@ static unsigned tile_parts(int64_t tiles) {
     return parts;
 }
 
-// One launch of the FP32 class GEMM: with D-hat or without.
+// One launch of the FP32 class GEMM: with D-hat or without, with the cut's tests
+// or in full.
 static void run_class_f32(const ProblemDesc &d, dim3 grid, hipStream_t st) {
-    if (d.outD) hipLaunchKernelGGL(k_class_f32<true>, grid, dim3(512), 0, st, d);
-    else hipLaunchKernelGGL(k_class_f32<false>, grid, dim3(512), 0, st, d);
+    if (d.outD && d.skip) hipLaunchKernelGGL((k_class_f32<true, true>), grid, dim3(512), 0, st, d);
+    else if (d.outD) hipLaunchKernelGGL((k_class_f32<true, false>), grid, dim3(512), 0, st, d);
+    else if (d.skip) hipLaunchKernelGGL((k_class_f32<false, true>), grid, dim3(512), 0, st, d);
+    else hipLaunchKernelGGL((k_class_f32<false, false>), grid, dim3(512), 0, st, d);
 }
 
 hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st) {
