@@ -95,14 +95,17 @@ struct BtnbArgs {
     const int32_t *blk_uid;
     double *outD;             // nullptr: B-hat^T N^-1 B-hat only
 };
-// Whether a radial cut, in mean pixel spacings (0: none), is short enough for a
-// form of the contraction (prec: 1 FP32, 2 or 3 BF16 parts) to test its MFMAs
-// against the masks.  Measured at lmax 1500, every MFMA / tests.  FP32: cut at 9
-// spacings 7.00 / 5.55 ms, at 15 6.99 / 7.37, the lines cross near 13; BF16x6: at
-// 9 4.81 / 4.44 ms, at 12 4.97 / 5.03, with D-hat at 9 5.86 / 5.58, at 10.8 5.99 /
-// 6.07; BF16x3: at 9 3.21 / 3.22, at 12 3.38 / 3.56, at lmax 480 already 0.549 /
-// 0.556 at 9.  (The FP64 form tests at every cut: 23.6 -> 21.8 ms at 15 spacings,
-// lmax 2048.)
+// Whether a radial cut, in mean pixel spacings (0: none; between two grids those
+// of the unknowns' grid), is short enough for a form of the contraction (prec: 1
+// FP32, 2 or 3 BF16 parts) to test its MFMAs against the masks.  Measured, every
+// MFMA / tests.  FP32, lmax 1500: cut at 9 spacings 7.00 / 5.57 ms, at 15 6.95 /
+// 7.37, the lines cross near 13; BF16x6: at 9 4.78 / 4.47, at 12 4.97 / 5.03, with
+// D-hat at 9 5.81 / 5.54, at 10.8 5.99 / 6.07; BF16x3: at 9 3.21 / 3.22, at 12
+// 3.38 / 3.56, at lmax 480 already 0.549 / 0.556 at 9, but at 6 (lmax 1024) 1.79
+// / 1.47, with D-hat (700) 1.19 / 1.03.  Two grids, lmax 256: FP32 at 12 (twice
+// the band limit) 2.49 / 2.39, BF16x6 at 9 (twice) 2.42 / 1.87, BF16x3 at 7.5 (1.5
+// times) 0.645 / 0.541.  (The FP64 form tests at every cut: 12.0 -> 11.0 ms at 15
+// spacings, lmax 1500.)
 inline bool short_cut(int prec, double spacings) {
     return spacings > 0 && spacings < (prec == 1 ? 12.5 : prec == 3 ? 10.0 : 8.0);
 }

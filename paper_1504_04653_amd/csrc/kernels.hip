@@ -196,9 +196,10 @@ __global__ __launch_bounds__(256) void k_unique_eval(KTable kt, const UInfo *__r
 // so the unique blocks are read once and the kernel only streams writes.  The
 // stored blocks of a band's unique blocks interleave in memory: each XCD takes
 // one contiguous range of the items, and 1024 threads write a block in two
-// stores each, so that what is written together lies together.  Measured,
-// lmax 1500 (8.5 GB): 1.58 -> 1.48 ms (256 threads, items in turn over the
-// XCDs, before); either change alone 1.54.
+// stores each, so that what is written together lies together.  Measured with
+// its tabulation against 256 threads and items in turn over the XCDs: lmax 400
+// 211 -> 204 us, 900 717 -> 697; at 1500 (8.5 GB) the gain, 1.68 -> 1.57 ms, is
+// less than runs of either differ by (12%).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void k_expand(const double *__restrict__ u64,
                                                 const int32_t *__restrict__ items,
@@ -328,10 +329,14 @@ __global__ __launch_bounds__(256) void k_convolve(const double *__restrict__ u64
 // (row-major FP64).  Chunk c of a tile is 16 bytes (c & 2047) of member row
 // c >> 11; a wave's 64 chunks lie in one row, so the row is uniform.  Step stp
 // of a workgroup of NT threads loads chunks [N NT stp, N NT (stp + 1)), N per
-// thread; they are stored one step later, right after that step's loads:
-// stores and loads share one wait counter, and a store placed there is waited
-// for only by the next step's operand wait.  sBlk[m] is the stored block of
-// member row m (-1: none), sBlk[64 + m] its unique D-hat block.
+// thread (past the tile's last chunk it reloads the first row's and stores
+// nothing).  The FP32 and split-BF16 forms store them one step later, right after
+// that step's loads: stores and loads share one wait counter, and a store placed
+// there is waited for only by the next step's operand wait.  The FP64 form
+// stores them at the end of their own step, after its barrier, where the
+// compiler's wait for them also empties the operand loads ahead of them.
+// sBlk[m] is the stored block of member row m (-1: none), sBlk[64 + m] its unique
+// D-hat block.
 // ---------------------------------------------------------------------------
 template <int N>
 struct DCopy {
@@ -424,7 +429,8 @@ __device__ __forceinline__ void empty_class_tile(const PD &pd, const DevClass &c
 // whatever rows and members share a tile.  A tile whose N^-1 holds an infinity
 // or NaN, and a kernel whose table overflowed, run the full lists, since there
 // a zero factor does not give a zero product.  MFMAs left (lmax 256, beam 3
-// pixels): 48%; units of four rings of a column would leave 55%.
+// pixels): 48%; units of four rings of a column would leave 55%.  A kernel without
+// a cut skips the masks and runs the full lists.
 //
 // The operands of a step are staged through LDS for all four waves (W of the
 // tile's rows, the B_IK values of all columns, the B_IJ values of the rows), by
@@ -940,8 +946,8 @@ void k_batch_f64(const ProblemDesc64 *__restrict__ probs, const int32_t *__restr
 // full contraction bit for bit.  An FP32 wave tests each MFMA (a unit of one
 // column group), a split-BF16 one each half term (its products are split and
 // scheduled together).  Measured, beam 3 pixels, lmax 1500, contraction: FP32
-// 7.00 -> 5.55 ms, BF16x6 4.92 -> 4.40; FP32 on the two-hop pattern (lmax 701,
-// 2.3 pixels) 3.06 -> 1.77.
+// 7.00 -> 5.57 ms, BF16x6 4.78 -> 4.47; FP32 on the two-hop pattern (lmax 701,
+// 2.3 pixels) 3.05 -> 1.78.
 struct SkipLds {
     uint16_t mask[kMaxClassTerms * 64];   // units of (term, row a) in which B_IJ is not all zero
     uint16_t cols[kMaxClassTerms * 4];    // units of (term, column group j) in which B_IK is not all zero
@@ -1015,7 +1021,7 @@ __device__ __forceinline__ void class_f32_tile(const ProblemDesc &pd, int item, 
                                                int32_t *sBlk, int32_t *sTerm, floatx4 *sW, floatx4 *sU, SkipLds *sk) {
     const float *__restrict__ ut32 = pd.ut32;
     double *__restrict__ out = pd.out;
-    constexpr int NW = 8, NT = 64 * NW, RP = NW / 2, RPW = 64 / RP;
+    constexpr int NW = 8, NT = 64 * NW, RP = NW / 2;
     const int tid = thread_index<BATCH>();
     const int cls = pd.mtiles[4 * item], m0 = pd.mtiles[4 * item + 1];
     const DevClass cl = pd.classes[cls];
@@ -1374,10 +1380,6 @@ __device__ __forceinline__ void split_pair(float y0, float y1, uint32_t *out) {
     }
 }
 
-__device__ __forceinline__ bf16x8 load_bf16x8(const uint16_t *p) {
-    return __builtin_bit_cast(bf16x8, *(const u16x8 *)p);
-}
-
 // N^-1 split into three BF16 parts (hi, mid, lo) from FP64, read directly as
 // MFMA operands by the class GEMM.
 __global__ __launch_bounds__(256) void k_split_ninv(const double *__restrict__ ninv, int64_t n,
@@ -1427,7 +1429,7 @@ __device__ __forceinline__ void class_bf16_tile(const ProblemDescB &pd, int item
     const int tid = thread_index<BATCH>();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int NW = 8, NT = 64 * NW;              // waves, threads
-    constexpr int RP = NW / 2, RPW = 64 / RP;          // row phases, rows per wave
+    constexpr int RP = NW / 2;                       // row phases
     const int rw = wave % RP, ch = wave / RP;          // row phase, column half
     const int lane = tid & 63, lr = lane & 15, lk = lane >> 4;
     const int nterms = cl.nterms;

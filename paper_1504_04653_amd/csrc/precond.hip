@@ -50,7 +50,8 @@ __device__ __forceinline__ void wave_sync() {
 // lk + 4 v of column 16 L + lr, as an MFMA result.  The element-by-element form
 // this replaces broadcast every multiplier from LDS to the 64 lanes (2016
 // doubles per tile, 32 k LDS clocks per four waves) and took 1.88 ms at lmax
-// 2048 (97,456 tiles); this takes 1.3, at 5.4 TB/s.
+// 2048 (97,456 tiles); this takes 1.3, at 5.4 TB/s.  With C the registers do not
+// quite hold it: 44 bytes per lane lie in scratch memory.
 template <bool WITH_C>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3))) void k_factor_diag(const double *__restrict__ D,
                                                              const double *__restrict__ C,

@@ -16,7 +16,7 @@
 //              ring's real values in pairs), the ring scattered to SymPix order
 //   k_ring_adj the transpose: gather, FFT, unfold to the modes m <= L
 //   k_leg_adj  one workgroup per m: a_lm = sum_rings lambda_lm G_m(ring),
-//              reduced across the workgroup eight degrees at a time
+//              reduced across the workgroup 8 or 16 degrees at a time
 //
 // lambda_lm is carried from lambda_mm (tabulated on the host) by the monic
 // form of its three-term recurrence in l, with a per-ring power-of-two scale
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256) void k_alm_mm(const double *__restrict__ src, 
 // the same for every ring: the kernels read them with uniform loads, which go
 // through the scalar cache into scalar registers.
 //
-// When |mu| has grown past 2^300 at a test (one per four or eight degrees),
+// When |mu| has grown past 2^300 at a test (one per 4, 8 or 16 degrees),
 // mu is scaled by 2^-300 and e raised by 300, so that the values far below the
 // double range near the poles at high m still reach the degrees where they
 // matter.  Between tests |mu| grows by less than 1.25 per degree (|cos| <= 1,
@@ -275,17 +275,17 @@ __global__ __launch_bounds__(kLegThreads) void k_leg_syn(ShtDesc d, const int64_
 }
 
 // ---------------------------------------------------------------------------
-// Legendre transpose.  Workgroup m; thread t carries the ring pairs t + 256 q
-// (q < R, R 256 >= nhalf), with G(north) +- G(south) scaled by 2^e, and adds
-// mu_i times them over its rings, eight degrees at a time; the workgroup then
-// sums the 256 partials of each of the 16 values (cos, sin x 8 degrees)
-// through LDS and wave shuffles, and the result times K_i^2 (K_i for lambda,
-// K_i for the stored scale) is written.  Degrees past L read b = 0 and are
-// not written.
+// Legendre transpose.  Workgroup m; thread t carries the ring pairs t + T q
+// (q < R, R T >= nhalf, T threads), with G(north) +- G(south) scaled by 2^e, and
+// adds mu_i times them over its rings, CH degrees at a time (8, or 16 where a
+// thread has one or two ring pairs); the workgroup then sums the T partials of
+// each of the 2 CH values (cos, sin x CH degrees) through LDS and wave shuffles,
+// and the result times K_i^2 (K_i for lambda, K_i for the stored scale) is
+// written.  Degrees past L read b = 0 and are not written.
 //
 // While a ring's e is below kEMin its terms are left out: there |lambda| <
-// 2^(e + 573) < 2^-387 (|mu| < 2^303 after a test, K < 2^270), far below the
-// rounding of any sum.  2^e G would underflow there; when a rescale lifts e to
+// 2^(e + 576) < 2^-384 (|mu| < 2^306 after a test, as 1.25^16 < 2^6; K < 2^270),
+// far below the rounding of any sum.  2^e G would underflow there; when a rescale lifts e to
 // kEMin or above, the ring's G is read again and scaled by the new 2^e.
 // ---------------------------------------------------------------------------
 constexpr int kEMin = -960;
