@@ -66,7 +66,7 @@ BOUND = {"fp64": 1e-10, "fp32": 1e-6, "bf16x6": 1e-6, "bf16x3": 2.0 ** -15}  # g
 DTYPE = {"fp64": "f64", "fp32": "f32", "bf16x6": "bf16", "bf16x3": "bf16"}
 HBM_PEAK = 8000.0                                                              # GB/s
 FP64_VECTOR = 78.6     # TFLOP/s: FP64 FMA on the vector ALUs (256 CUs x 4 SIMDs x 16 lanes x 2 x 2.4 GHz)
-KERNEL_NAME = {"fp64": "k_class_f64<false>", "fp32": "k_class_f32<false>", "bf16x3": "k_class_bf16<2, false>",
+KERNEL_NAME = {"fp64": "k_class_f64<false, false>", "fp32": "k_class_f32<false, true>", "bf16x3": "k_class_bf16<2, false>",
                "bf16x6": "k_class_bf16<3, false>"}
 BATCH_KERNEL = {"fp64": "k_batch_f64", "fp32": "k_batch_f32", "bf16x6": "k_batch_bf16<3>",
                 "bf16x3": "k_batch_bf16<2>"}

@@ -527,7 +527,7 @@ __device__ __forceinline__ bool not_finite(double v) {
     return ((uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32) & 0x7ff00000u) == 0x7ff00000u;
 }
 
-template <int NI, bool WD, bool BATCH>
+template <int NI, bool WD, bool ALL, bool BATCH>
 __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item, int part, int parts, const F64Lds &lds) {
     constexpr int R = f64_rows(NI);
     constexpr int kWRows = NI == 4 ? 64 : 32;    // rows of W staged
@@ -561,7 +561,7 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
     for (int x = tid; x < 2 * nterms; x += 256) lds.term[x] = terms[x];
     // A kernel without a cut has no zeros worth a look: every step runs in full,
     // and nothing is asked of N^-1 (lmax 256 with 512: 3363 -> 3287 us)
-    bool all = pd.cut == 0;
+    bool all = ALL || pd.cut == 0;
     if (!all) {
         for (int x = tid; x < 32 * nterms; x += 256)                       // 64 masks of 2 bytes per term
             ((uint32_t *)lds.mask)[x] = ((const uint32_t *)pd.units)[(int64_t)terms[2 * (x >> 5)] * 32 + (x & 31)];
@@ -795,7 +795,7 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
                     for (int t = 0; t < 2; ++t)
 #pragma unroll
                         for (int q = 0; q < NR * NJ; ++q)
-                            if (on & (1u << (4 * q + 2 * h + t))) {
+                            if (ALL || (on & (1u << (4 * q + 2 * h + t)))) {
                                 const double bv = u1[q / NJ][t] * u2[SYM ? q % NJ : q & 3][t];
 #pragma unroll
                                 for (int i = 0; i < NI; ++i)
@@ -865,7 +865,11 @@ __device__ __forceinline__ void class_f64_tile(const ProblemDesc64 &pd, int item
     }
 }
 
-template <bool WD>
+// ALL: for kernels without a cut, every MFMA and no test of them.  Measured
+// against tests that all say yes / the full contraction that loaded its operands
+// per wave: lmax 1500 11.42 / 12.0 -> 11.15 ms, lmax 512 with 1126 24.2 / 22.3 ->
+// 21.7, 256 with 589 5.85 / 5.70 -> 5.27.
+template <bool WD, bool ALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_class_f64(ProblemDesc64 pd) {
     extern __shared__ __align__(16) char smem[];
@@ -873,9 +877,9 @@ void k_class_f64(ProblemDesc64 pd) {
     const int item = blockIdx.x;        // pd.mtiles: a dispatch table, slot per workgroup
     const int groups = pd.mtiles[4 * item + 2];
     if (groups == 0) return;            // an empty slot
-    if (groups == 4) class_f64_tile<4, WD, false>(pd, item, blockIdx.y, gridDim.y, lds);
-    else if (groups == 2) class_f64_tile<2, WD, false>(pd, item, blockIdx.y, gridDim.y, lds);
-    else class_f64_tile<1, WD, false>(pd, item, blockIdx.y, gridDim.y, lds);
+    if (groups == 4) class_f64_tile<4, WD, ALL, false>(pd, item, blockIdx.y, gridDim.y, lds);
+    else if (groups == 2) class_f64_tile<2, WD, ALL, false>(pd, item, blockIdx.y, gridDim.y, lds);
+    else class_f64_tile<1, WD, ALL, false>(pd, item, blockIdx.y, gridDim.y, lds);
 }
 
 // Queue draining shared by the persistent batch kernels: thread 0 takes the
@@ -919,9 +923,9 @@ void k_batch_f64(const ProblemDesc64 *__restrict__ probs, const int32_t *__restr
         const ProblemDesc64 pd = probs[items[2 * at]];
         const int item = items[2 * at + 1];
         const int groups = pd.mtiles[4 * item + 2];
-        if (groups == 4) class_f64_tile<4, false, true>(pd, item, part, parts, lds);
-        else if (groups == 2) class_f64_tile<2, false, true>(pd, item, part, parts, lds);
-        else class_f64_tile<1, false, true>(pd, item, part, parts, lds);
+        if (groups == 4) class_f64_tile<4, false, false, true>(pd, item, part, parts, lds);
+        else if (groups == 2) class_f64_tile<2, false, false, true>(pd, item, part, parts, lds);
+        else class_f64_tile<1, false, false, true>(pd, item, part, parts, lds);
     }
 }
 
@@ -1875,6 +1879,13 @@ static unsigned tile_parts(int64_t tiles) {
     return parts;
 }
 
+// The kernel of one FP64 launch: with D-hat or without, with the cut's tests or
+// without.
+static void (*class_f64_kernel(const ProblemDesc64 &d))(ProblemDesc64) {
+    if (d.outD) return d.cut ? k_class_f64<true, false> : k_class_f64<true, true>;
+    return d.cut ? k_class_f64<false, false> : k_class_f64<false, true>;
+}
+
 // One launch of the FP32 class GEMM: with D-hat or without, with the cut's tests
 // or in full.
 static void run_class_f32(const ProblemDesc &d, dim3 grid, hipStream_t st) {
@@ -1890,12 +1901,11 @@ hipError_t launch_btnb(int prec, const BtnbArgs &a, hipStream_t st) {
         ProblemDesc64 pd{a.mtiles, a.classes, a.class_terms, a.class_blk, a.class_itab, a.u64t, a.ninv, a.out,
                          a.du64, a.blk_uid, a.outD, a.masks.units, a.masks.cols, a.masks.overflow, a.max_terms, a.tile_rows, a.cut};
         const int lds = f64_lds_bytes(a.max_terms, a.tile_rows);
-        const void *k = a.outD ? (const void *)k_class_f64<true> : (const void *)k_class_f64<false>;
-        const hipError_t e = f64_allow_lds(k, lds);
+        const auto k = class_f64_kernel(pd);
+        const hipError_t e = f64_allow_lds((const void *)k, lds);
         if (e != hipSuccess) return e;
         const dim3 grid((unsigned)a.nmtiles, f64_parts(a.nmtiles, a.max_terms));
-        if (a.outD) hipLaunchKernelGGL(k_class_f64<true>, grid, dim3(256), lds, st, pd);
-        else hipLaunchKernelGGL(k_class_f64<false>, grid, dim3(256), lds, st, pd);
+        hipLaunchKernelGGL(k, grid, dim3(256), lds, st, pd);
         return hipGetLastError();
     }
     if (prec == 1) {
@@ -1946,7 +1956,7 @@ hipError_t launch_batch(const BatchLaunch &b, hipStream_t st) {
                 if (b.ngtiles[p] == 0) continue;
                 ProblemDesc64 d = b.host_desc64[p];
                 d.mtiles = b.gtiles[p];
-                hipLaunchKernelGGL(k_class_f64<false>, dim3((unsigned)b.ngtiles[p], f64_parts(b.ngtiles[p], b.max_terms)), dim3(256),
+                hipLaunchKernelGGL(class_f64_kernel(d), dim3((unsigned)b.ngtiles[p], f64_parts(b.ngtiles[p], b.max_terms)), dim3(256),
                                    f64_lds_bytes(d.max_terms, d.tile_rows), st, d);
             }
         }
@@ -1997,7 +2007,8 @@ hipError_t batch_prepare(int prec, int max_terms, int *workgroups_per_cu) {
     if (prec == 0) {
         const int lds = f64_lds_bytes(max_terms, 64);
         hipError_t e = f64_allow_lds((const void *)k_batch_f64, lds);
-        if (e == hipSuccess) e = f64_allow_lds((const void *)k_class_f64<false>, lds);
+        if (e == hipSuccess) e = f64_allow_lds((const void *)k_class_f64<false, false>, lds);
+        if (e == hipSuccess) e = f64_allow_lds((const void *)k_class_f64<false, true>, lds);
         if (e != hipSuccess) return e;
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(workgroups_per_cu, k_batch_f64, 256, lds);
     }
